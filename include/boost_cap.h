@@ -302,10 +302,10 @@ int boost_prefetch(boost_ctx *ctx, const boost_tensor *view, void *stream);
  *     workgroups, dispatched first, stream every host-page unit while all
  *     other workgroups stream HBM-page units, so host and HBM reads overlap in
  *     every wave (§3 "CAP").  host_workers = 0 picks the default: n_cu / 16
- *     for the GEMV (B <= 6); for the matrix-core kernels one worker per 16
+ *     for the GEMV; for the matrix-core kernels one worker per 16
  *     host units of the tensor, at least n_cu / 16 and at most n_cu / 8
- *     (from B = 17 a host unit is one 16-row tile of a work unit, so a host
- *     page spreads over more workers).  Never more workers than host units. */
+ *     (a host unit is one 16-row tile of a page, so a host page spreads over
+ *     more workers).  Never more workers than host units. */
 #define BOOST_SCHED_ADDRESS 0
 #define BOOST_SCHED_CAP 1
 int boost_gemv_set_schedule(boost_ctx *ctx, int schedule, int host_workers);
@@ -317,7 +317,8 @@ int boost_gemv_set_schedule(boost_ctx *ctx, int schedule, int host_workers);
  * bf16 rounded to nearest even (BOOST_DTYPE_BF16).  Accumulation is fp32 and
  * the reduction order is fixed, so results are bitwise reproducible and do
  * not depend on the placement or the schedule.  1 <= B <= 256, K % 8 == 0,
- * N >= 1.  Batches up to 6 run as a GEMV on the vector units; larger ones as a
+ * N >= 1.  Batches up to 3 (1 on matrices of 2^26 elements or
+ * more) run as a GEMV on the vector units; larger ones as a
  * skinny GEMM on the matrix cores (the batch sizes of §5.10), with
  * the same page-confined work units; a matrix too small to fill the GPU at a
  * large batch has K split over several workgroups whose partials go to a

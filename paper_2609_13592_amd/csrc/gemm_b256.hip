@@ -1,0 +1,5 @@
+// The matrix-core GEMM of 16 batch tiles (one translation unit per count, so
+// that they build in parallel).
+#include "gemm.h"
+
+template int bst::gv::launch_gemm<16>(GemvParams&, int, bool, const boost_ctx*, hipStream_t);

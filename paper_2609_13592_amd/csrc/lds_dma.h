@@ -15,8 +15,8 @@ constexpr int vmcnt_imm() {
   return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8);
 }
 
-// 16 bytes per lane from buffer resource r at byte offset off into LDS at
-// lds_block + 16 lane (lds_block uniform over the wavefront).  M0 is set here
+// 16 bytes per lane from buffer resource r at byte offset off into LDS at byte
+// address lds_addr + 16 lane (lds_addr uniform over the wavefront).  M0 is set here
 // and declared clobbered; nothing else in these kernels uses M0 (clang warns
 // that a reserved register is clobbered, which is the intent).  One wait
 // state separates the M0 write from the load that reads it, as the compiler
@@ -26,11 +26,19 @@ constexpr int vmcnt_imm() {
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void load16_lds(__amdgpu_buffer_rsrc_t r, uint32_t off,
-                                           const char* lds_block) {
-  typedef __attribute__((address_space(3))) const char* lds_ptr;  // LDS byte address
-  const uint32_t la = __builtin_amdgcn_readfirstlane(
-      static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_ptr)lds_block)));
+                                           uint32_t lds_addr) {
+  const uint32_t la = __builtin_amdgcn_readfirstlane(lds_addr);
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+               :
+               : "s"(la), "v"(off), "s"(r)
+               : "memory", "m0");
+}
+// The same with the streaming (non-temporal) policy, for bytes that are read
+// once, so that the caches keep what is read again.
+__device__ __forceinline__ void load16_lds_nt(__amdgpu_buffer_rsrc_t r, uint32_t off,
+                                              uint32_t lds_addr) {
+  const uint32_t la = __builtin_amdgcn_readfirstlane(lds_addr);
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds"
                :
                : "s"(la), "v"(off), "s"(r)
                : "memory", "m0");

@@ -208,6 +208,44 @@ def test_mfma_placement_invariance_and_parity(gpu_ctx, N, K, B):
         assert np.array_equal(y.view(np.uint32), outs[0].view(np.uint32))
 
 
+# One shape for every unit of the matrix-core GEMM and every edge of its
+# dispatch: units of several pages whose count is no multiple of theirs and
+# whose pages lie on both tiers (23096 and 28672 columns: four, 13696: two),
+# 1, 2, 4, 5 and 8 row tiles a page, rows that share cache lines (K % 64), slices
+# with a ragged last stage, N % 4 != 0 (single stores), both sides of the
+# few-rows kernel and of the GEMV's batch range.
+@pytest.mark.parametrize("N,K,B", [(230, 23096, 20), (190, 28672, 130), (420, 13696, 33),
+                                   (1300, 5000, 4), (1200, 3000, 4), (1201, 3000, 16),
+                                   (901, 9000, 16), (2304, 5120, 64), (640, 8192, 17),
+                                   (3000, 1032, 5), (77, 14336, 65), (6000, 72, 40)])
+def test_gemm_units_invariance_and_parity(gpu_ctx, N, K, B):
+    """Every unit shape of the matrix-core GEMM: the fp32 summation bound
+    against the oracle, and the same bits under all-HBM, alternating, modulo
+    and all-host maps and under both schedules."""
+    w, x = synth.gemv_inputs(17 * N + K + B, N, K, B)
+    n = opl.n_pages(w.nbytes)
+    maps = {"hbm": np.zeros(n, np.uint8), "alt": (np.arange(n) % 2).astype(np.uint8),
+            "mpp3": opl.mpp_tier_map(w.nbytes, 3), "irregular": irregular_map(n),
+            "host": np.ones(n, np.uint8)}
+    xd = to_dev_u16(x)
+    first = None
+    for name, tiers in maps.items():
+        t = place(gpu_ctx, w, tiers=tiers)
+        try:
+            for sched in (bd.SCHED_CAP, bd.SCHED_ADDRESS):
+                bd.boost_gemv_set_schedule(gpu_ctx, sched, 0)
+                y = run_gemv(gpu_ctx, t, N, K, xd, B)
+                if first is None:
+                    first = y
+                    assert_f32_bound(y, w, x)
+                    yb = run_gemv(gpu_ctx, t, N, K, xd, B, bd.DTYPE_BF16)
+                    assert np.array_equal(yb, og.f32_to_bf16(y))
+                assert np.array_equal(y.view(np.uint32), first.view(np.uint32)), (name, sched)
+        finally:
+            bd.boost_gemv_set_schedule(gpu_ctx, bd.SCHED_CAP, 0)
+            bd.boost_tensor_free(t)
+
+
 @pytest.mark.parametrize("B", [9, 16, 256])
 def test_mfma_exact_pins(gpu_ctx, B):
     """W = I gives x back exactly on the matrix-core path; bf16 output of it
