@@ -56,6 +56,12 @@ static_assert(kMaxPartBlocks <= kThreads, "one thread per partition size");
 #define BOOST_ATTN_PART_MAX 256
 #endif
 constexpr int kPartMin = BOOST_ATTN_PART_MIN, kPartMax = BOOST_ATTN_PART_MAX;
+// ... but while such items are fewer than the compute units they are halved,
+// down to four blocks: a longer chain of loads on some units is then worse
+// than the starts and ends of more items (32 / 8 heads, one request of 500 /
+// 2048 tokens: 16.6 / 17.1 -> 10.0 / 11.6 us, four of 200..1000: 16.8 -> 11.4;
+// with enough items it loses, one of 8192: 19.2 -> 20.7).
+constexpr int kPartFew = 4;
 
 struct AttnParams {
   // Linear placement makes the tier of a pool page a fixed function of its
@@ -230,16 +236,19 @@ __device__ __forceinline__ void consume(const uint32_t (*qp)[4], const uint4* kb
   }
 }
 
-// Head-distributed softmax for G = 2 and 4.  The G partial dot products of a
-// lane (its 8 dimensions of one token, every query head) are reduced over
-// the token's 16 lanes by a transposing butterfly: exchange with the lane
-// xor 1 (and xor 2 for G = 4) keeping half the heads each time, then add the
-// lanes 4 and 8 apart, so each lane ends with the full score of ONE head
-// (head_of_lane) instead of every lane holding all G.  The running maximum,
-// the exponentials and the running sum are then computed once per head and
-// token instead of 16 times; the probabilities and rescale factors reach the
-// other lanes' accumulators by quad broadcasts.  Same online softmax as
-// consume(), fewer vector instructions per block.
+// Head-distributed softmax for G = 2, 4 and 8 (8 as two groups of four heads).
+// The partial dot products of a lane (its 8 dimensions of one token, every
+// query head) are reduced over the token's 16 lanes by a transposing
+// butterfly: exchange with the lane xor 1 (and xor 2 for groups of four)
+// keeping half the heads each time, then add the lanes 4 and 8 apart, so each
+// lane ends with the full score of ONE head of a group (head_of_lane) instead
+// of every lane holding all of them.  The running maximum, the exponentials
+// and the running sum are then computed once per head and token instead of 16
+// times; the probabilities and rescale factors reach the other lanes'
+// accumulators by quad broadcasts.  Same online softmax as consume(), fewer
+// vector instructions per block (at G = 8, 190 -> 140).
+template <int G>
+constexpr int hd_group() { return G == 8 ? 4 : G; }
 template <int G>
 __device__ __forceinline__ int head_of_lane(int lane) {
   const int i = lane & 3;
@@ -280,50 +289,104 @@ __device__ __forceinline__ float score_of_lane_head(const float* d, bool b0, boo
   return f;
 }
 
-template <int G, int U, bool MASKED, typename AfterK>
-__device__ __forceinline__ void consume_hd(const uint32_t (*qp)[4], const uint4* kb,
+// factor of every head of every group in every lane of a quad
+template <int G>
+__device__ __forceinline__ void bcast_groups(const float* v, float* out) {
+  constexpr int Q = hd_group<G>();
+#pragma unroll
+  for (int i = 0; i < G / Q; ++i) bcast_heads<Q>(v[i], out + i * Q);
+}
+
+template <int G, int U, bool MASKED, typename Query, typename AfterK>
+__device__ __forceinline__ void consume_hd(Query query, const uint4* kb,
                                            const uint4* vb, const bool* valid, float sc2,
-                                           bool b0, bool b1, float& mh, float& lh,
+                                           bool b0, bool b1, float* mh, float* lh,
                                            float (*acc)[8], AfterK after_k) {
-  float s[U];
+  constexpr int Q = hd_group<G>(), N = G / Q;  // heads of a group, groups
+  float s[U][N];
 #pragma unroll
-  for (int u = 0; u < U; ++u) {
-    float d[G];
+  for (int i = 0; i < N; ++i) {
+    uint4 q[Q];
 #pragma unroll
-    for (int j = 0; j < G; ++j) {
-      float x = dot2(qp[j][0], kb[u].x, 0.f);
-      x = dot2(qp[j][1], kb[u].y, x);
-      x = dot2(qp[j][2], kb[u].z, x);
-      d[j] = dot2(qp[j][3], kb[u].w, x);
+    for (int j = 0; j < Q; ++j) q[j] = query(i * Q + j);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      float d[Q];
+#pragma unroll
+      for (int j = 0; j < Q; ++j) {
+        float x = dot2(q[j].x, kb[u].x, 0.f);
+        x = dot2(q[j].y, kb[u].y, x);
+        x = dot2(q[j].z, kb[u].z, x);
+        d[j] = dot2(q[j].w, kb[u].w, x);
+      }
+      const float f = score_of_lane_head<Q>(d, b0, b1) * sc2;
+      s[u][i] = (!MASKED || valid[u]) ? f : -INFINITY;
     }
-    const float f = score_of_lane_head<G>(d, b0, b1) * sc2;
-    s[u] = (!MASKED || valid[u]) ? f : -INFINITY;
+    if constexpr (N > 1) __builtin_amdgcn_sched_barrier(0);  // (registers)
   }
   after_k();  // the K registers are free from here on
-  float mc = mh;
+  float c[N], cj[G];
 #pragma unroll
-  for (int u = 0; u < U; ++u) mc = fmaxf(mc, s[u]);
-  // nothing valid yet for this head: keep the state (factor 1)
-  const float c = (MASKED && mc == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f(mh - mc);
-  lh *= c;
-  mh = mc;
-  float cj[G];
-  bcast_heads<G>(c, cj);
+  for (int i = 0; i < N; ++i) {
+    float mc = mh[i];
+#pragma unroll
+    for (int u = 0; u < U; ++u) mc = fmaxf(mc, s[u][i]);
+    // nothing valid yet for this head: keep the state (factor 1)
+    c[i] = (MASKED && mc == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f(mh[i] - mc);
+    lh[i] *= c[i];
+    mh[i] = mc;
+  }
+  bcast_groups<G>(c, cj);
 #pragma unroll
   for (int j = 0; j < G; ++j)
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[j][e] *= cj[j];
 #pragma unroll
   for (int u = 0; u < U; ++u) {
-    const float p = (MASKED && s[u] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(s[u] - mh);
-    lh += p;
-    float pj[G], vf[8];
-    bcast_heads<G>(p, pj);
+    float p[N], pj[G], vf[8];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      p[i] = (MASKED && s[u][i] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(s[u][i] - mh[i]);
+      lh[i] += p[i];
+    }
+    bcast_groups<G>(p, pj);
     unpack8(vb[u], vf);
 #pragma unroll
     for (int j = 0; j < G; ++j)
 #pragma unroll
       for (int e = 0; e < 8; ++e) acc[j][e] = fmaf(pj[j], vf[e], acc[j][e]);
+    if constexpr (N > 1) __builtin_amdgcn_sched_barrier(0);  // (registers)
+  }
+}
+
+// slot_merge for the head-distributed state: the factors once per head.
+template <int G, int D>
+__device__ __forceinline__ void slot_merge_hd(float* mh, float* lh, float (*acc)[8]) {
+  constexpr int N = G / hd_group<G>();
+  float c1[N], c2[N], c1j[G], c2j[G];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    float m1, m2, l1, l2;
+    pair_of<D>(mh[i], m1, m2);
+    pair_of<D>(lh[i], l1, l2);
+    const float M = fmaxf(m1, m2);
+    // both empty: factors 1 on zero sums
+    c1[i] = M == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m1 - M);
+    c2[i] = M == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m2 - M);
+    lh[i] = l1 * c1[i] + l2 * c2[i];
+    mh[i] = M;
+  }
+  bcast_groups<G>(c1, c1j);
+  bcast_groups<G>(c2, c2j);
+#pragma unroll
+  for (int j = 0; j < G; ++j) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      float a1, a2;
+      pair_of<D>(acc[j][e], a1, a2);
+      acc[j][e] = a1 * c1j[j] + a2 * c2j[j];
+    }
+    __builtin_amdgcn_sched_barrier(0);  // one head's pairs at a time in registers
   }
 }
 
@@ -385,6 +448,76 @@ __device__ __forceinline__ void find_request(const AttnParams& P, int target, in
     if (carry > target) break;  // uniform
   }
   __syncthreads();
+}
+
+// The item of item_of (below) for at most 64 requests: one request per lane,
+// every wavefront by itself, with ballots instead of barriers (0.9 us less
+// before an item's first loads).
+__device__ __forceinline__ bool item_of_wave(const AttnParams& P, int idx, int& b, int& g,
+                                             int& part, int& L) {
+  const int lane = threadIdx.x & 63, PB = P.part_blocks, H = P.H;
+  const int L0 = lane < P.B ? P.lens[lane] : 0;
+  const int n = L0 <= 0 ? 0 : min((L0 + kT - 1) / kT, P.max_blocks);
+  const int full = n / PB, rem = n % PB;
+  // inclusive prefix sums of both counts over the requests
+  int xf = full, xr = rem > 0;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int yf = __shfl_up(xf, d, 64), yr = __shfl_up(xr, d, 64);
+    if (lane >= d) {
+      xf += yf;
+      xr += yr;
+    }
+  }
+  const int F = __builtin_amdgcn_readlane(xf, 63), R = __builtin_amdgcn_readlane(xr, 63);
+  auto pick = [&](unsigned long long who) {
+    b = __builtin_amdgcn_readfirstlane(static_cast<int>(__ffsll(who)) - 1);
+    L = __builtin_amdgcn_readlane(L0, b);
+  };
+  if (idx < F + R) {  // every partition of head H-1
+    const int end = xf + xr, beg = end - full - (rem > 0);
+    const unsigned long long who = __ballot(beg <= idx && idx < end);
+    if (!who) return false;
+    pick(who);
+    part = idx - __builtin_amdgcn_readlane(beg, b);
+    g = H - 1;
+    return true;
+  }
+  int j = idx - (F + R);
+  if (j < (H - 1) * F) {  // full partitions of the others
+    const int t = j / (H - 1);
+    const unsigned long long who = __ballot(xf - full <= t && t < xf);
+    if (!who) return false;
+    pick(who);
+    part = t - __builtin_amdgcn_readlane(xf - full, b);
+    g = H - 2 - j % (H - 1);
+    return true;
+  }
+  j -= (H - 1) * F;
+  if (j >= (H - 1) * R) return false;
+  // partial partitions by size: the rank-th largest rem (below 256), bit by
+  // bit, then the requests of that size in order
+  int rank = j / (H - 1);
+  unsigned long long who = __ballot(rem > 0);
+#pragma unroll
+  for (int bit = 7; bit >= 0; --bit) {
+    const unsigned long long ones = who & __ballot(rem >> bit & 1);
+    const int c = __popcll(ones);
+    if (rank < c) {
+      who = ones;
+    } else {
+      rank -= c;
+      who &= ~ones;
+    }
+  }
+  const int before = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(who >> 32),
+                                               __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(who), 0));
+  const unsigned long long one = __ballot((who >> lane & 1) && before == rank);
+  if (!one) return false;
+  pick(one);
+  part = __builtin_amdgcn_readlane(full, b);
+  g = H - 2 - j % (H - 1);
+  return true;
 }
 
 // Work item of workgroup idx, from the context lengths alone (so the same on
@@ -463,19 +596,18 @@ __device__ bool item_of(const AttnParams& P, int idx, int& b, int& g, int& part,
   return true;
 }
 
-// Waves per SIMD the register allocator targets for G <= 4: three (168
-// registers, no spill) against the two it picks by itself took config 3 from
-// 136 to 126 us; four spill and run at 306 us.  G = 8 keeps the allocator's
-// own choice (a tighter target spills its accumulators).
+// Waves per SIMD the register allocator targets: three for G <= 4 (168
+// registers; against the two it picks by itself this took config 3 from 136 to
+// 126 us; four spill and run at 306 us), two for G = 8 (225 registers; the
+// 302 of the kernel that kept every head's score in every lane and the queries
+// in registers left one, and took 41 us for 8 requests of 2048 tokens with 64 /
+// 8 heads, 149 us for 32 of 512..4096, against 27.5 and 96).
 #ifndef BOOST_ATTN_WAVES
 #define BOOST_ATTN_WAVES 3
 #endif
-#ifndef BOOST_ATTN_HD
-#define BOOST_ATTN_HD 1
-#endif
-template <int G>
+template <int G, bool WAVE>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
-    G == 8 ? 1 : BOOST_ATTN_WAVES))) void attn_partition(AttnParams P) {
+    G == 8 ? 2 : BOOST_ATTN_WAVES))) void attn_partition(AttnParams P) {
   constexpr int kUnroll = G == 8 ? BOOST_ATTN_UNROLL8 : BOOST_ATTN_UNROLL;  // blocks in flight
   __shared__ float s_ml[4][G][2];
   __shared__ float s_acc[4][G][kD];
@@ -488,7 +620,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
   __shared__ int32_t row[kMaxPartBlocks];
   __shared__ int s_red[4], s_pick[5];
   int part, b, g, L;
-  if (!item_of(P, blockIdx.x, b, g, part, L, s_red, row, s_pick)) return;  // uniform
+  if constexpr (WAVE) {
+    if (!item_of_wave(P, blockIdx.x, b, g, part, L)) return;  // uniform
+  } else {
+    if (!item_of(P, blockIdx.x, b, g, part, L, s_red, row, s_pick)) return;  // uniform
+  }
   const int n_blk = L <= 0 ? 0 : min((L + kT - 1) / kT, P.max_blocks);
   const int blk_beg = part * P.part_blocks;
   if (blk_beg >= n_blk) return;  // uniform: empty partition (not produced by item_of)
@@ -496,23 +632,42 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
   // leading blocks whose 16 tokens are all inside the context
   const int nfull = max(0, min(nbp, L / kT - blk_beg));
   const uint64_t head_off = static_cast<uint64_t>(g) * P.nb * (kT * kD * 2);
+  // q stays in bf16 pairs for the dot2 instruction
+  // (G = 8: in LDS, since the accumulators and a group's K and V leave no
+  // registers for them at three waves per SIMD)
+  constexpr bool kQLds = G == 8;
+  __shared__ uint4 s_q[kQLds ? G * kLanesTok : 1];
+  uint32_t qp[kQLds ? 1 : G][4];
+  if constexpr (kQLds) {
+    if (tid < G * kLanesTok)
+      s_q[tid] = *reinterpret_cast<const uint4*>(
+          P.q + (static_cast<int64_t>(b) * P.Hq + g * G) * kD + tid * 8);
+  } else {
+#pragma unroll
+    for (int j = 0; j < G; ++j) {
+      const uint4 u = *reinterpret_cast<const uint4*>(
+          P.q + (static_cast<int64_t>(b) * P.Hq + g * G + j) * kD + dc * 8);
+      qp[j][0] = u.x;
+      qp[j][1] = u.y;
+      qp[j][2] = u.z;
+      qp[j][3] = u.w;
+    }
+  }
+  auto query = [&](int j) {
+    if constexpr (kQLds) {
+      int at = dc;
+      asm volatile("" : "+v"(at));  // read where it is used, not once for the whole item
+      return s_q[j * kLanesTok + at];
+    } else {
+      return make_uint4(qp[j][0], qp[j][1], qp[j][2], qp[j][3]);
+    }
+  };
   // the partition's width of the table row (entries past the context are
   // read but not used)
   if (tid < min(P.part_blocks, P.max_blocks - blk_beg))
     row[tid] = P.tables[static_cast<int64_t>(b) * P.max_blocks + blk_beg + tid];
   __syncthreads();
 
-  // q stays in bf16 pairs for the dot2 instruction
-  uint32_t qp[G][4];
-#pragma unroll
-  for (int j = 0; j < G; ++j) {
-    const uint4 u = *reinterpret_cast<const uint4*>(
-        P.q + (static_cast<int64_t>(b) * P.Hq + g * G + j) * kD + dc * 8);
-    qp[j][0] = u.x;
-    qp[j][1] = u.y;
-    qp[j][2] = u.z;
-    qp[j][3] = u.w;
-  }
   const float sc2 = P.scale * 1.4426950408889634f;  // log2(e)
   float m[G], l[G], acc[G][8];
 #pragma unroll
@@ -523,9 +678,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
     for (int e = 0; e < 8; ++e) acc[j][e] = 0.f;
   }
   // head-distributed state (G = 2, 4): this lane's head's maximum and sum
-  constexpr bool kHD = BOOST_ATTN_HD && (G == 2 || G == 4);
+  constexpr bool kHD = G >= 2;
+  constexpr int kHG = kHD ? G / hd_group<G>() : 1;
   const bool b0 = tid & 1, b1 = tid & 2;
-  float mh = -INFINITY, lh = 0.f;
+  float mh[kHG], lh[kHG];
+#pragma unroll
+  for (int i = 0; i < kHG; ++i) {
+    mh[i] = -INFINITY;
+    lh[i] = 0.f;
+  }
 
   const uint32_t lane_off = static_cast<uint32_t>(tid) * 16;
   // address of head-block (g, blk) of K and V: uniform scalar arithmetic
@@ -575,9 +736,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
       };
       if constexpr (kHD) {
         if (all_ok)
-          consume_hd<G, kUnroll, false>(qp, kb, vb, valid, sc2, b0, b1, mh, lh, acc, next_k);
+          consume_hd<G, kUnroll, false>(query, kb, vb, valid, sc2, b0, b1, mh, lh, acc, next_k);
         else
-          consume_hd<G, kUnroll, true>(qp, kb, vb, valid, sc2, b0, b1, mh, lh, acc, next_k);
+          consume_hd<G, kUnroll, true>(query, kb, vb, valid, sc2, b0, b1, mh, lh, acc, next_k);
       } else {
         if (all_ok)
           consume<G, kUnroll, false>(qp, kb, vb, valid, sc2, m, l, acc, next_k);
@@ -605,13 +766,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
       valid[u] = ok && (blk_beg + i + u) * kT + ts < L;
     }
     if constexpr (kHD)
-      consume_hd<G, kUnroll, true>(qp, kb, vb, valid, sc2, b0, b1, mh, lh, acc, none);
+      consume_hd<G, kUnroll, true>(query, kb, vb, valid, sc2, b0, b1, mh, lh, acc, none);
     else
       consume<G, kUnroll, true>(qp, kb, vb, valid, sc2, m, l, acc, none);
-  }
-  if constexpr (kHD) {  // every head's maximum and sum in every lane again
-    bcast_heads<G>(mh, m);
-    bcast_heads<G>(lh, l);
   }
 
   // merge the 4 slots of a wavefront (lanes 16 and 32 apart hold the same
@@ -619,8 +776,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
   // lane the pair (v of the lower lane, v of the lane 16 above it) of its
   // 16-apart pair, permlane32_swap the same for lanes 32 apart, so both
   // lanes of a pair merge the same two states in the same order
-  slot_merge<G, 16>(m, l, acc);
-  slot_merge<G, 32>(m, l, acc);
+  if constexpr (kHD) {
+    slot_merge_hd<G, 16>(mh, lh, acc);
+    slot_merge_hd<G, 32>(mh, lh, acc);
+    bcast_groups<G>(mh, m);  // every head's maximum and sum in every lane again
+    bcast_groups<G>(lh, l);
+  } else {
+    slot_merge<G, 16>(m, l, acc);
+    slot_merge<G, 32>(m, l, acc);
+  }
   const int wave = tid >> 6, lane = tid & 63;
   if (lane < kLanesTok) {
 #pragma unroll
@@ -726,8 +890,16 @@ template <int G>
 int launch(AttnParams& P, hipStream_t s) {
   const int64_t grid = static_cast<int64_t>(P.H) * P.B * P.n_parts;
   if (grid > 0x7fffffff) return bst::fail(BOOST_EINVAL, "grid too large");
-  hipLaunchKernelGGL(attn_partition<G>, dim3(static_cast<unsigned>(grid)), dim3(kThreads),
-                     0, s, P);
+  // up to 64 requests the search by wavefronts, in a kernel of its own (64
+  // requests of 512..4096 tokens, 32 / 8 heads: 106.7 us, 108.4 with the search
+  // by barriers, 111.0 with both in one kernel, whose registers spill; one of
+  // 8192: 18.5 and 19.4)
+  if (P.B <= 64)
+    hipLaunchKernelGGL((attn_partition<G, true>), dim3(static_cast<unsigned>(grid)),
+                       dim3(kThreads), 0, s, P);
+  else
+    hipLaunchKernelGGL((attn_partition<G, false>), dim3(static_cast<unsigned>(grid)),
+                       dim3(kThreads), 0, s, P);
   BOOST_HIP(hipGetLastError());
   hipLaunchKernelGGL(attn_merge, dim3(static_cast<unsigned>(P.B * P.Hq)), dim3(64), 0, s, P);
   BOOST_HIP(hipGetLastError());
@@ -795,9 +967,13 @@ int decode(boost_ctx* ctx, const boost_kv_pool* pool, int layer, const void* q, 
   // wave is short), each long enough to amortise its start and its merge
   // (PART_MIN blocks) and short enough to balance (PART_MAX blocks)
   const int want_parts = std::max(1, (BOOST_ATTN_ITEMS + B * H - 1) / (B * H));
+  int part_min = kPartMin;
+  while (part_min > kPartFew &&
+         static_cast<int64_t>(B) * H * ((max_blocks + part_min - 1) / part_min) < ctx->n_cu)
+    part_min /= 2;
   P.part_blocks = std::min(
       {kMaxPartBlocks, max_blocks,
-       std::max(kPartMin, std::min(kPartMax, (max_blocks + want_parts - 1) / want_parts))});
+       std::max(part_min, std::min(kPartMax, (max_blocks + want_parts - 1) / want_parts))});
   P.part_blocks = std::max(P.part_blocks, 4);
   P.n_parts = (max_blocks + P.part_blocks - 1) / P.part_blocks;
   P.max_parts = max_parts > 0 ? max_parts : P.n_parts;

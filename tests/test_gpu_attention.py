@@ -93,6 +93,38 @@ def test_more_than_256_requests(gpu_ctx, Hq, H):
     assert np.array_equal(outs[1].view(np.uint32), outs[0].view(np.uint32))
 
 
+# Both sides of the two item searches (64 requests), of the halved partitions
+# (items fewer than compute units: 16-, 8- and 4-block partitions) and every
+# head group, with empty contexts and partial blocks among them.
+@pytest.mark.parametrize("Hq,H,B,hi", [(32, 8, 64, 300), (32, 8, 65, 300), (64, 8, 64, 200),
+                                       (64, 8, 1, 4096), (64, 8, 3, 900), (32, 8, 1, 500),
+                                       (32, 8, 1, 1), (16, 8, 2, 1100), (8, 8, 1, 2048),
+                                       (4, 4, 5, 700), (16, 2, 7, 600)])
+def test_item_search_and_partitions(gpu_ctx, Hq, H, B, hi):
+    rng = np.random.default_rng(hi + B)
+    lengths = rng.integers(1, hi, size=B, endpoint=True)
+    lengths[0] = hi
+    lengths[3::9] = 0
+    _, q, ks, vs = synth.attention_inputs(B, Hq, H, 128, 0, 0, seed=B, kv_seed=hi,
+                                          lengths=lengths)
+    ref = oa.decode_attention(q, ks, vs)
+    nb = int(sum((int(L) + 15) // 16 for L in lengths)) + 64
+    outs = []
+    for mode, M in ((bd.KV_ALL_HBM, 0), (bd.KV_LPP, 3)):
+        pool = new_pool(gpu_ctx, H, Hq, nb, M, mode, max_batch=B,
+                        max_blocks=(hi + 15) // 16)
+        try:
+            tables = fill_pool(bd, gpu_ctx, pool, 0, lengths, ks, vs)
+            o = run_attn(gpu_ctx, pool, 0, q, tables, lengths)
+            assert og.rel_err(o, ref) <= TOL
+            assert np.max(np.abs(o - ref)) < 1e-4
+            assert np.all(o[lengths == 0] == 0)
+            outs.append(o)
+        finally:
+            bd.boost_kv_pool_destroy(pool)
+    assert np.array_equal(outs[1].view(np.uint32), outs[0].view(np.uint32))
+
+
 def test_host_heads_follow_block_types(gpu_ctx):
     """LPP with H = 8 and a modulus above H: the tail lies in head 7, so an SHH
     request has exactly its head-7 data on host; output still exact."""
