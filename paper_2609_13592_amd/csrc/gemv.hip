@@ -455,27 +455,13 @@ __global__ __launch_bounds__(kThreads) void mfma_kernel(GemvParams P) {
 // y of a split-K call: the S slice partials of every (batch row, row) in
 // slice order; a row cut by a page boundary adds its earlier page's slices,
 // then its later page's.
-__device__ __forceinline__ float cut_row_sum(const GemvParams& P, int b, int64_t p1) {
-  const float* cut = P.ws + static_cast<int64_t>(P.S) * P.B * P.N;
-  float part0[kMaxSlices], part1[kMaxSlices];
-#pragma unroll
-  for (int s = 0; s < kMaxSlices; ++s) {
-    part0[s] = s < P.S ? cut[((p1 * 2 + 0) * P.S + s) * P.B + b] : 0.f;
-    part1[s] = s < P.S ? cut[((p1 * 2 + 1) * P.S + s) * P.B + b] : 0.f;
-  }
-  float v = 0.f, v1 = 0.f;
-#pragma unroll
-  for (int s = 0; s < kMaxSlices; ++s)
-    if (s < P.S) {
-      v += part0[s];
-      v1 += part1[s];
-    }
-  return v + v1;
-}
-
+//
 // One lane per (b, V consecutive n): V = 4 where rows of y and of the slices
-// are 16-byte aligned (6144 x 4096 at 256 rows, four slices: 6.1 us, and 7.1
-// with one n a lane for half the slices), else 1.
+// are 16-byte aligned and four rows end on at most one other page (6144 x 4096
+// at 256 rows, four slices: 6.1 us, and 7.1 with one n a lane for half the
+// slices), else 1.  Every load goes out before the sums (a loop over a run-time
+// S would wait for each in turn; a cut row found by division and loaded after
+// the others cost 4096 x 14336 at 24 rows 29.2 us a call against 27.8).
 template <int V>
 __global__ __launch_bounds__(256) void split_reduce(GemvParams P) {
   const int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
@@ -484,30 +470,48 @@ __global__ __launch_bounds__(256) void split_reduce(GemvParams P) {
   const int b = static_cast<int>(t / nv);
   const int64_t r0 = (t - static_cast<int64_t>(b) * nv) * V;
   typedef __attribute__((ext_vector_type(V))) float vec_t;
-  // all S loads go out together (a loop over a run-time S would wait for
-  // each in turn), then the sums in slice order
   vec_t part[kMaxSlices];
 #pragma unroll
   for (int s = 0; s < kMaxSlices; ++s)
     part[s] = s < P.S ? *reinterpret_cast<const vec_t*>(
                             P.ws + (static_cast<int64_t>(s) * P.B + b) * P.N + r0)
                       : vec_t(0.f);
+  // the one page that begins inside these rows, if any: `in` elements after
+  // their start, in the row `cut` unless it begins with a row
+  const int64_t e0 = r0 * P.K, p = e0 / kPageElems + 1;
+  const int64_t in = p * kPageElems - e0;
+  int cut = -1;
+  float part0[kMaxSlices], part1[kMaxSlices];
+  if (in < static_cast<int64_t>(V) * P.K) {
+    const int d = static_cast<int>(in);
+    int i = 0;
+#pragma unroll
+    for (int k = 1; k < V; ++k) i += d >= k * P.K;
+    if (d != i * P.K) {
+      cut = i;
+      const float* q = P.ws + static_cast<int64_t>(P.S) * P.B * P.N + p * 2 * P.S * P.B + b;
+#pragma unroll
+      for (int s = 0; s < kMaxSlices; ++s) {
+        part0[s] = s < P.S ? q[static_cast<int64_t>(s) * P.B] : 0.f;
+        part1[s] = s < P.S ? q[static_cast<int64_t>(P.S + s) * P.B] : 0.f;
+      }
+    }
+  }
   vec_t v = vec_t(0.f);
 #pragma unroll
   for (int s = 0; s < kMaxSlices; ++s)
     if (s < P.S) v += part[s];
-  if (kPageElems % P.K != 0) {  // uniform: some rows are cut
-    // the pages that begin inside these rows (one at most, unless a page
-    // holds fewer than V rows), so that lanes with a cut row sum it together
-    const int64_t e0 = r0 * P.K, last = (e0 + V * static_cast<int64_t>(P.K) - 1) / kPageElems;
-    for (int64_t p = e0 / kPageElems + 1; p <= last; ++p) {
-      const int64_t e = p * kPageElems, r = e / P.K;
-      if (r * P.K == e) continue;  // the page begins with a row
-      const float c = cut_row_sum(P, b, p);
+  if (cut >= 0) {
+    float v0 = 0.f, v1 = 0.f;
 #pragma unroll
-      for (int i = 0; i < V; ++i)
-        if (r == r0 + i) v[i] = c;
-    }
+    for (int s = 0; s < kMaxSlices; ++s)
+      if (s < P.S) {
+        v0 += part0[s];
+        v1 += part1[s];
+      }
+#pragma unroll
+    for (int e = 0; e < V; ++e)
+      if (e == cut) v[e] = v0 + v1;
   }
   if (V == 4 && !P.y_bf16) {
     *reinterpret_cast<vec_t*>(static_cast<float*>(P.y) + static_cast<int64_t>(b) * P.N + r0) = v;
@@ -602,7 +606,8 @@ int64_t rows_met(const GemvParams& P, int n_pages) {
 int launch_sums(GemvParams& P, int n_pages, bool need_fixup, hipStream_t s) {
   if (P.S > 1) {
     if (P.slices) return BOOST_OK;  // the consumer sums the slices
-    const bool vec = P.N % 4 == 0 && (P.y_bf16 || (reinterpret_cast<uintptr_t>(P.y) & 15) == 0);
+    const bool vec = P.N % 4 == 0 && P.K <= kPageElems / 4 &&
+                     (P.y_bf16 || (reinterpret_cast<uintptr_t>(P.y) & 15) == 0);
     const int64_t lanes = static_cast<int64_t>(P.B) * (vec ? P.N / 4 : P.N);
     const dim3 grid(static_cast<unsigned>((lanes + 255) / 256));
     if (vec)
