@@ -310,6 +310,26 @@ int boost_prefetch(boost_ctx *ctx, const boost_tensor *view, void *stream);
 #define BOOST_SCHED_CAP 1
 int boost_gemv_set_schedule(boost_ctx *ctx, int schedule, int host_workers);
 
+/* The kernel of a decode GEMV call and how it is cut.  Planned from the sizes
+ * (BOOST_KERNEL_AUTO), or set for every later call on a context so that tests
+ * and measurements reach each one at any size: the GEMV (up to 3 batch rows),
+ * the kernel of 16-row units (up to 16), or the GEMM with units of `row_tiles`
+ * 16-row tiles of each of `pages` consecutive pages (8 x 1, 8 x 2, 3 x 4,
+ * 5 x 1, 4 x 1, 2 x 1, 1 x 1; several pages only where no page meets more rows
+ * than that, 1 x 1 up to 32 batch rows), with K cut into `slices` (1, 2, 4 or
+ * 8; those of fewer than 512 columns, or more than the workspace holds, do not
+ * fit).  A call that does not fit what is set fails with EINVAL. */
+#define BOOST_KERNEL_AUTO 0
+#define BOOST_KERNEL_GEMV 1
+#define BOOST_KERNEL_ROWS16 2
+#define BOOST_KERNEL_GEMM 3
+int boost_gemv_set_route(boost_ctx *ctx, int kernel, int row_tiles, int pages, int slices);
+/* What is planned for [N, K] at batch B (max_slices = 0: boost_decode_gemv,
+ * else boost_decode_gemv_slices; host-only arithmetic, a plan-only context
+ * plans for 256 compute units).  Errors: EINVAL. */
+int boost_gemv_route(const boost_ctx *ctx, int N, int K, int B, int max_slices,
+                     int *kernel, int *row_tiles, int *pages, int *slices);
+
 /* y[b, n] = sum_k W[n, k] * x[b, k] (§3.1 handwritten matmul; §4.4 up/down
  * projections).  W: placed tensor holding an [N, K] row-major bf16 matrix
  * (nn.Linear layout; bytes must equal N*K*2).  x: device bf16 [B, K]

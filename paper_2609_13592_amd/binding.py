@@ -24,6 +24,7 @@ TIER_HBM, TIER_HOST = 0, 1
 PLACE_MPP, PLACE_MPP_GLOBAL, PLACE_LINEAR, PLACE_RANDOM = 0, 1, 2, 3
 DTYPE_F32, DTYPE_BF16 = 0, 1
 SCHED_ADDRESS, SCHED_CAP = 0, 1
+KERNEL_AUTO, KERNEL_GEMV, KERNEL_ROWS16, KERNEL_GEMM = 0, 1, 2, 3
 PAGE_BYTES = 2 * 1024 * 1024
 
 _vp = C.c_void_p
@@ -86,6 +87,8 @@ _SIGS = {
     "boost_tensor_read": (_i32, [_vp, _u64, _vp, _u64]),
     "boost_tensor_free": (_i32, [_vp]),
     "boost_gemv_set_schedule": (_i32, [_vp, _i32, _i32]),
+    "boost_gemv_set_route": (_i32, [_vp, _i32, _i32, _i32, _i32]),
+    "boost_gemv_route": (_i32, [_vp, _i32, _i32, _i32, _i32] + [C.POINTER(_i32)] * 4),
     "boost_embed_gather": (_i32, [_vp, _vp, _i32, _i32, _vp, _i32, _vp, _vp]),
     "boost_rmsnorm": (_i32, [_vp, _vp, _vp, _i32, _i32, C.c_float, _vp, _vp]),
     "boost_add_rmsnorm": (_i32, [_vp, _vp, _vp, _vp, _i32, _i32, C.c_float, _vp, _vp]),
@@ -371,6 +374,18 @@ def boost_prefetch(ctx: int, view: int, stream=None):
 # -------------------------------------------------------------------- GEMV
 def boost_gemv_set_schedule(ctx: int, schedule: int, host_workers: int = 0):
     _check(load().boost_gemv_set_schedule(ctx, schedule, host_workers))
+
+
+def boost_gemv_set_route(ctx: int, kernel: int, row_tiles: int = 0, pages: int = 0,
+                         slices: int = 1):
+    _check(load().boost_gemv_set_route(ctx, kernel, row_tiles, pages, slices))
+
+
+def boost_gemv_route(ctx: int, N: int, K: int, B: int, max_slices: int = 0):
+    """(kernel, row_tiles, pages, slices) that a call of these sizes runs with."""
+    r = [_i32() for _ in range(4)]
+    _check(load().boost_gemv_route(ctx, N, K, B, max_slices, *map(C.byref, r)))
+    return tuple(v.value for v in r)
 
 
 def boost_decode_gemv(ctx: int, W: int, N: int, K: int, x, B: int, y,

@@ -36,8 +36,8 @@
 // two pages of 8192 columns (57344 x 8192, 256 rows: 257 us, 287 with one
 // page), four of 28672 (8192 x 28672, 64 rows: 85 us; 131 with 64-row units).
 #include <algorithm>
-#include <cmath>
 
+#include "gemm_plan.h"
 #include "gemv_common.h"
 #include "lds_dma.h"
 
@@ -45,8 +45,6 @@ namespace bst {
 namespace gv {
 namespace {
 
-constexpr int kDmaBlk = 1024;  // 8 rows x 128 bytes
-constexpr int kDmaLds = 163840;  // LDS of a compute unit
 // The 2-D arrangement of the NW wavefronts over a unit's G pages of RTL row
 // tiles and BT batch tiles (16 row groups + batch groups): the one with the
 // fewest products per wavefront, then the fewest fragments read per 32-column
@@ -61,41 +59,6 @@ constexpr int dma_wave_grid() {
       if (c < cost) best = 16 * wr + wb, cost = c;
     }
   return best;
-}
-// Wavefronts of a workgroup (eight where the products weigh, four otherwise:
-// 10240 x 8192 at 8 rows 29.4 us with four, 31.6 with eight; 28672 x 4096 at
-// 256 rows 74 us with eight, 82 with four), and the stages of x and of W in
-// its rings: 8..16 of both while two workgroups fit a compute unit (small
-// units live off their depth), else four of x and up to seven of W, three and
-// two of x where it takes 32 KiB a stage.
-constexpr int gemm_waves(int bt, int rtl, int g) {
-  if (g > 1) return 8;
-  if (rtl == 5) return bt == 4 ? 4 : 8;
-  return rtl >= 8 ? (bt >= 8 ? 8 : 4) : (bt >= 16 && rtl >= 4 ? 8 : 4);
-}
-constexpr int gemm_x_stages(int bt, int rows) {
-  const int small = 80 / (2 * bt + 2 * rows);
-  if (small >= 8) return small < 16 ? small : 16;
-  return bt >= 16 ? (rows > 12 ? 2 : 3) : 4;
-}
-constexpr int gemm_w_stages(int bt, int rows) {
-  const int xs = gemm_x_stages(bt, rows);
-  if (xs >= 8) return xs;
-  const int fit = (kDmaLds / kDmaBlk - xs * 2 * bt) / (2 * rows);
-  return fit < 7 ? fit : 7;
-}
-// A host sub-unit (one row tile) loads W in spans of kSpan stages, 512 bytes of
-// a row at a time: the link carries those faster than 128-byte reads (6144 x
-// 4096 with one page of 24 on host, 8 rows: 45 us against 59; 57344 x 8192 with
-// three of 448: 143 against 156).  Two spans in its ring; three and four took
-// 1-9 % longer, the HBM units beside them most.
-constexpr int kSpan = 4, kHostSpans = 2;
-// Workgroups that a compute unit holds at once.
-constexpr int gemm_occupancy(int bt, int rtl, int g) {
-  const int rows = g * rtl;
-  const int kib = gemm_x_stages(bt, rows) * 2 * bt + gemm_w_stages(bt, rows) * 2 * rows;
-  const int lds = kDmaLds / kDmaBlk / kib, waves = 16 / gemm_waves(bt, rtl, g);
-  return lds < waves ? lds : waves;
 }
 template <int BT, int RTL, int G, int NW>
 struct GemmCfg {
@@ -487,60 +450,16 @@ int launch_gemm_shape(GemvParams& P, int n_pages, bool need_fixup, const boost_c
   return launch_sums(P, n_pages, need_fixup, s);
 }
 
-// The unit shapes: row tiles of a page, and pages.
-struct GemmShape {
-  int rtl, g;
-};
-constexpr GemmShape kGemmShapes[] = {{8, 1}, {8, 2}, {3, 4}, {5, 1}, {4, 1}, {2, 1}, {1, 1}};
-
 }  // namespace
 
-// Picks the unit and the K slices by an estimate of the call's time in us, from
-// times of every unit and split of 18 matrices at 8..200 batch rows; the pick
-// is within 6 % of the fastest on most of them.  A compute unit passes about
-// 45 KiB of stages a us (35 where W's ring has three stages or fewer), W is read at
-// 6.8 TB/s at most, a workgroup takes at least `lat` us a stage (its ring over
-// the loads' latency, and the barrier), and split sums cost a launch and their
-// traffic.  16-row units are for few batch rows only: at more, x's traffic is
-// the unit's.
 template <int BT>
-int launch_gemm(GemvParams& P, int n_pages, bool need_fixup, const boost_ctx* ctx,
-                hipStream_t s) {
-  const int64_t most = rows_met(P, n_pages);
-  const double cu = ctx->n_cu;
-  const uint64_t per = static_cast<uint64_t>(P.B) * (P.N + 2ull * (n_pages + 1));
-  const double hbm = 2e-6 / 6.8 * P.N * P.K;  // us to read W
-  double best = 1e30;
-  int pick = -1, S = 1;
-  for (int i = 0; i < static_cast<int>(sizeof kGemmShapes / sizeof *kGemmShapes); ++i) {
-    const int rtl = kGemmShapes[i].rtl, g = kGemmShapes[i].g;
-    const int64_t upp = (most + 16 * rtl - 1) / (16 * rtl);
-    if ((g > 1 && upp != 1) || (rtl == 1 && BT > 2)) continue;
-    const int64_t units = (n_pages + g - 1) / g * upp;
-    const int occ = gemm_occupancy(BT, rtl, g);
-    const double kb = 2 * g * rtl + 2 * BT;  // KiB of a stage
-    const double lat = std::max(BT <= 2 && rtl == 5 ? 0.42 : 0.18, 1.5 / gemm_w_stages(BT, g * rtl));
-    for (int c = 1; c <= kMaxSlices; c *= 2) {
-      if (c > 1 && (P.K / c < 512 || c * per > ctx->gemm_ws_floats)) break;
-      const double nst = (P.K / c + 63) / 64, wgs = static_cast<double>(units) * c;
-      const double bytes = std::ceil(wgs / cu) * nst * kb / (gemm_w_stages(BT, g * rtl) > 3 ? 45 : 35);
-      const double rounds = std::ceil(wgs / (cu * occ));
-      const double sums = c > 1 ? 2 + 8e-6 / 4.5 * c * P.B * P.N : 0;
-      const double t = std::max({hbm, bytes, rounds * nst * lat}) + rounds * 1.5 + sums;
-      if (t < best) best = t, pick = i, S = c;
-    }
-  }
-  while (S > 1 && P.slices && S * per > static_cast<uint64_t>(P.slice_floats)) S /= 2;
-  P.S = S;
-  if (S > 1) P.ws = P.slices ? P.slices : ctx->gemm_ws;
-  const int rtl = kGemmShapes[pick].rtl;
-  P.units_per_page = static_cast<int>((most + 16 * rtl - 1) / (16 * rtl)) * S;
-  switch (pick) {
+int launch_gemm(GemvParams& P, const Route& route, int n_pages, bool need_fixup,
+                const boost_ctx* ctx, hipStream_t s) {
+  switch (route.shape) {
     case 0: return launch_gemm_shape<BT, 8, 1>(P, n_pages, need_fixup, ctx, s);
     case 1: return launch_gemm_shape<BT, 8, 2>(P, n_pages, need_fixup, ctx, s);
     case 2: return launch_gemm_shape<BT, 3, 4>(P, n_pages, need_fixup, ctx, s);
-    case 3:
-      return launch_gemm_shape<BT, 5, 1>(P, n_pages, need_fixup, ctx, s);
+    case 3: return launch_gemm_shape<BT, 5, 1>(P, n_pages, need_fixup, ctx, s);
     case 4: return launch_gemm_shape<BT, 4, 1>(P, n_pages, need_fixup, ctx, s);
     case 5: return launch_gemm_shape<BT, 2, 1>(P, n_pages, need_fixup, ctx, s);
     default:

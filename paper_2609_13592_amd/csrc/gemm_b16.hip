@@ -2,4 +2,5 @@
 // that they build in parallel).
 #include "gemm.h"
 
-template int bst::gv::launch_gemm<1>(GemvParams&, int, bool, const boost_ctx*, hipStream_t);
+template int bst::gv::launch_gemm<1>(GemvParams&, const Route&, int, bool, const boost_ctx*,
+                                      hipStream_t);

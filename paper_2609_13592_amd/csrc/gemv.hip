@@ -663,43 +663,21 @@ int launch(GemvParams& P, int n_pages, bool need_fixup, const boost_ctx* ctx, hi
   return launch_sums(P, n_pages, need_fixup, s);
 }
 
-// Rows up to which mfma_kernel takes the matrix-core calls of up to 16 batch
-// rows (both sides measured: see mfma_kernel).
-constexpr int kFewRows = 1200;
-
 int launch_mfma(GemvParams& P, int n_pages, bool need_fixup, const boost_ctx* ctx,
                 hipStream_t s) {
+  const int S = P.S;
   P.units_per_page = static_cast<int>((rows_met(P, n_pages) + 15) / 16);
-  // split K until there are two workgroups per CU, in slices of at least 512
-  // columns whose partials fit the context's workspace or the caller's buffer
-  const int64_t units = static_cast<int64_t>(n_pages) * P.units_per_page;
-  const uint64_t per = static_cast<uint64_t>(P.B) * (P.N + 2ull * (n_pages + 1));
-  const uint64_t cap = P.slices ? static_cast<uint64_t>(P.slice_floats) : ctx->gemm_ws_floats;
-  int S = 1;
-  while (S < kMaxSlices && units * S < 2 * ctx->n_cu && P.K / (2 * S) >= 512) S *= 2;
-  while (S > 1 && S * per > cap) S /= 2;
   // host workers are counted over the units of whole rows
   P.S = 1;
   int64_t grid = plan_grid(P, n_pages, ctx, true);
   if (grid < 0) return bst::fail(BOOST_EINVAL, "grid too large");
   P.S = S;
   P.units_per_page *= S;
-  if (S > 1) P.ws = P.slices ? P.slices : ctx->gemm_ws;
   grid = P.host_workers +
          static_cast<int64_t>(P.address_order ? n_pages : P.n_hbm_pages) * P.units_per_page;
   hipLaunchKernelGGL(mfma_kernel, dim3(static_cast<unsigned>(grid)), dim3(kThreads), 0, s, P);
   BOOST_HIP(hipGetLastError());
   return launch_sums(P, n_pages, need_fixup, s);
-}
-
-// Whether a call runs on the matrix cores (the others on the GEMV): from four
-// batch rows (28672 x 4096 at 4 / 6 rows: 38.1 / 38.1 us against 43.6 / 50.1;
-// 4096 x 4096 at 6: 10.9 against 15.5; 5003 x 3080 at 4: 16.4 against 17.3),
-// and at two and three on matrices of 2^26 elements or more (28672 x 4096 at
-// 2: 38.2 against 41.8 us, 8192 x 28672: 76.4 against 82.6; smaller ones lose
-// to the split sums' launch, 5003 x 3080 at 2: 17.3 against 11.3).
-bool matrix_cores(int N, int K, int B) {
-  return B >= 4 || (B >= 2 && static_cast<int64_t>(N) * K >= (int64_t{1} << 26));
 }
 
 template <int B>
@@ -721,6 +699,15 @@ namespace {
 int dispatch(GemvParams& P, const boost_tensor* W, int K, int B, const boost_ctx* ctx,
              hipStream_t s);
 
+int check_sizes(int N, int K, int B) {
+  if (N < 1 || K < 8 || K % 8) return fail(BOOST_EINVAL, "N=%d K=%d (K %% 8 == 0)", N, K);
+  if (static_cast<uint64_t>(K) * 2 > kPage)
+    return fail(BOOST_EINVAL, "row of %d elements exceeds a page", K);
+  if (B < 1 || B > kMaxGemvBatch)
+    return fail(BOOST_EINVAL, "B=%d outside [1, %d]", B, kMaxGemvBatch);
+  return BOOST_OK;
+}
+
 // The decode GEMV behind both entry points: y, or with `slices` the split-K
 // partial sums in fp32 in the layout of ws (S reported through n_slices).
 int decode_gemv(boost_ctx* ctx, const boost_tensor* W, int N, int K, const void* x, int B,
@@ -728,11 +715,7 @@ int decode_gemv(boost_ctx* ctx, const boost_tensor* W, int N, int K, const void*
                 void* stream) {
   if (!ctx || !W || !x || !y) return fail(BOOST_EINVAL, "null argument");
   if (ctx->device < 0) return fail(BOOST_ENODEV, "plan-only context");
-  if (N < 1 || K < 8 || K % 8) return fail(BOOST_EINVAL, "N=%d K=%d (K %% 8 == 0)", N, K);
-  if (static_cast<uint64_t>(K) * 2 > kPage)
-    return fail(BOOST_EINVAL, "row of %d elements exceeds a page", K);
-  if (B < 1 || B > kMaxGemvBatch)
-    return fail(BOOST_EINVAL, "B=%d outside [1, %d]", B, kMaxGemvBatch);
+  if (int rc = check_sizes(N, K, B)) return rc;
   if (y_dtype != BOOST_DTYPE_F32 && y_dtype != BOOST_DTYPE_BF16)
     return fail(BOOST_EINVAL, "y_dtype %d", y_dtype);
   if (static_cast<uint64_t>(N) * K * 2 != W->bytes)
@@ -771,22 +754,27 @@ int dispatch(GemvParams& P, const boost_tensor* W, int K, int B, const boost_ctx
   const int n = static_cast<int>(W->n_pages);
   P.n_pages = n;
   P.tiers = W->d_tiers;
-  if (matrix_cores(P.N, K, B)) {
+  const PlanInput in{P.N, K, B, n, rows_met(P, n), ctx->n_cu, ctx->gemm_ws_floats,
+                     P.slices != nullptr, static_cast<uint64_t>(P.slice_floats)};
+  const Route route = ctx->gemv_route.kernel ? forced_route(in, ctx->gemv_route) : plan(in);
+  if (route.kernel == kAuto)
+    return fail(BOOST_EINVAL, "N=%d K=%d B=%d does not fit the route that was set", P.N, K, B);
+  if (route.kernel != kGemv) {
     // every row cut by a page boundary goes through split_fixup
     P.join = 0;
     bool fix = false;
     for (int b = 1; b < n && !fix; ++b) fix = (static_cast<int64_t>(b) * kPageElems) % K != 0;
-    switch ((B + 15) / 16) {
-      case 1:
-        return P.N <= kFewRows ? launch_mfma(P, n, fix, ctx, s) : launch_gemm<1>(P, n, fix, ctx, s);
-      case 2: return launch_gemm<2>(P, n, fix, ctx, s);
-      case 3:
-      case 4: return launch_gemm<4>(P, n, fix, ctx, s);
-      case 5:
-      case 6:
-      case 7:
-      case 8: return launch_gemm<8>(P, n, fix, ctx, s);
-      default: return launch_gemm<16>(P, n, fix, ctx, s);
+    P.S = route.S;
+    if (P.S > 1) P.ws = P.slices ? P.slices : ctx->gemm_ws;
+    if (route.kernel == kFewRowsKernel) return launch_mfma(P, n, fix, ctx, s);
+    const int rows = 16 * kGemmShapes[route.shape].rtl;
+    P.units_per_page = static_cast<int>((in.most + rows - 1) / rows) * P.S;
+    switch (batch_tiles(B)) {
+      case 1: return launch_gemm<1>(P, route, n, fix, ctx, s);
+      case 2: return launch_gemm<2>(P, route, n, fix, ctx, s);
+      case 4: return launch_gemm<4>(P, route, n, fix, ctx, s);
+      case 8: return launch_gemm<8>(P, route, n, fix, ctx, s);
+      default: return launch_gemm<16>(P, route, n, fix, ctx, s);
     }
   }
   // split_fixup is needed only where a cut row crosses a tier boundary
@@ -816,6 +804,44 @@ int boost_gemv_set_schedule(boost_ctx* ctx, int schedule, int host_workers) {
   return BOOST_OK;
 }
 
+int boost_gemv_set_route(boost_ctx* ctx, int kernel, int row_tiles, int pages, int slices) {
+  if (!ctx) return fail(BOOST_EINVAL, "null ctx");
+  if (kernel < kAuto || kernel > kGemm) return fail(BOOST_EINVAL, "kernel %d", kernel);
+  if (kernel >= kFewRowsKernel &&
+      (slices < 1 || slices > kMaxSlices || (slices & (slices - 1))))
+    return fail(BOOST_EINVAL, "slices %d", slices);
+  bool known = kernel != kGemm;
+  for (const GemmShape& u : kGemmShapes) known = known || (u.rtl == row_tiles && u.g == pages);
+  if (!known) return fail(BOOST_EINVAL, "no unit of %d row tiles and %d pages", row_tiles, pages);
+  ctx->gemv_route = Forced{kernel, row_tiles, pages, slices};
+  return BOOST_OK;
+}
+
+int boost_gemv_route(const boost_ctx* ctx, int N, int K, int B, int max_slices, int* kernel,
+                     int* row_tiles, int* pages, int* slices) {
+  if (!ctx || !kernel || !row_tiles || !pages || !slices)
+    return fail(BOOST_EINVAL, "null argument");
+  if (int rc = check_sizes(N, K, B)) return rc;
+  if (max_slices < 0 || max_slices > BOOST_MAX_GEMV_SLICES)
+    return fail(BOOST_EINVAL, "max_slices %d outside [0, %d]", max_slices, BOOST_MAX_GEMV_SLICES);
+  uint64_t floats = 0;
+  if (max_slices > 0)
+    if (int rc = boost_gemv_slices_floats(N, K, B, max_slices, &floats)) return rc;
+  GemvParams P{};
+  P.N = N;
+  P.K = K;
+  const int64_t pages_ = (static_cast<int64_t>(N) * K + kPageElems - 1) / kPageElems;
+  if (pages_ > 0x7fffffff) return fail(BOOST_EINVAL, "N=%d K=%d", N, K);
+  const int n = static_cast<int>(pages_);
+  const PlanInput in{N, K, B, n, rows_met(P, n), ctx->device < 0 ? 256 : ctx->n_cu,
+                     ctx->device < 0 ? kGemmWsFloats : ctx->gemm_ws_floats, max_slices > 0, floats};
+  const Route r = plan(in);
+  *kernel = r.kernel;
+  *row_tiles = r.kernel == kGemm ? kGemmShapes[r.shape].rtl : (r.kernel == kFewRowsKernel ? 1 : 0);
+  *pages = r.kernel == kGemv ? 0 : (r.kernel == kGemm ? kGemmShapes[r.shape].g : 1);
+  *slices = r.S;
+  return BOOST_OK;
+}
 
 int boost_decode_gemv(boost_ctx* ctx, const boost_tensor* W, int N, int K, const void* x,
                       int B, void* y, int y_dtype, void* stream) {

@@ -2,6 +2,7 @@
 // parameters of a call, page lookups, buffer resources, and the host side of
 // a launch.
 #pragma once
+#include "gemm_plan.h"
 #include "runtime.h"
 
 namespace bst {
@@ -127,8 +128,6 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc_uniform(const void* 
 // 2 MiB, x is at most 8 * 512 K elements), so the load returns zero.
 constexpr uint32_t kOOB = 0x80000000u;
 
-// Most K slices a call splits a row group into.
-constexpr int kMaxSlices = 8;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 
@@ -143,7 +142,8 @@ int launch_sums(GemvParams& P, int n_pages, bool need_fixup, hipStream_t s);
 
 // The matrix-core GEMM for BT batch tiles of 16 rows (gemm_*.hip).
 template <int BT>
-int launch_gemm(GemvParams& P, int n_pages, bool need_fixup, const boost_ctx* ctx, hipStream_t s);
+int launch_gemm(GemvParams& P, const Route& route, int n_pages, bool need_fixup,
+                const boost_ctx* ctx, hipStream_t s);
 
 }  // namespace gv
 }  // namespace bst

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include "common.h"
+#include "gemm_plan.h"
 
 #define BOOST_HIP(call)                                                     \
   do {                                                                      \
@@ -19,6 +20,7 @@ struct boost_ctx {
   int host_numa = BOOST_NUMA_DEVICE;  // node that host-tier pages are bound to
   int gemv_schedule = BOOST_SCHED_CAP;
   int gemv_host_workers = 0;  // 0: default
+  bst::gv::Forced gemv_route;  // kernel and unit asked for (default: planned)
   // split-K partials of the matrix-core GEMM (slices of K run by different
   // workgroups; a second kernel sums them in slice order)
   float* gemm_ws = nullptr;

@@ -201,3 +201,36 @@ def test_plan_contrast_bad_arguments():
         bd.boost_plan_contrast(bd.PLACE_RANDOM, opl.PAGE, 4)
     with pytest.raises(ValueError):
         bd.boost_plan_contrast(bd.PLACE_RANDOM, 3 * opl.PAGE, 4, 0, np.zeros(2))
+
+
+def test_gemv_route_query():
+    """The planned route of a call: within what the kernels are built for, the
+    caller's slices a bound on K's, and bad sizes, kernels and units refused."""
+    ctx = bd.boost_init(-1)
+    try:
+        for N, K in ((64, 512), (1200, 3000), (1201, 3000), (5003, 3080), (4096, 14336),
+                     (57344, 8192), (8192, 28672), (1, 8)):
+            for B in (1, 2, 3, 4, 16, 17, 64, 65, 128, 129, 256):
+                kernel, rows, pages, S = bd.boost_gemv_route(ctx, N, K, B)
+                if kernel == bd.KERNEL_GEMV:
+                    assert B <= 3 and (rows, pages, S) == (0, 0, 1)
+                elif kernel == bd.KERNEL_ROWS16:
+                    assert B <= 16 and (rows, pages) == (1, 1)
+                else:
+                    assert kernel == bd.KERNEL_GEMM
+                    assert (rows, pages) in ((8, 1), (8, 2), (3, 4), (5, 1), (4, 1), (2, 1), (1, 1))
+                    assert pages == 1 or -(-opl.PAGE // (2 * K)) <= 16 * rows
+                assert S in (1, 2, 4, 8) and (S == 1 or K // S >= 512)
+                for cap in (1, 2, 4, 8):
+                    assert bd.boost_gemv_route(ctx, N, K, B, cap)[3] <= cap
+        for bad in ((0, 512, 1), (64, 12, 1), (64, 512, 0), (64, 512, 257)):
+            with pytest.raises(bd.BoostError) as e:
+                bd.boost_gemv_route(ctx, *bad)
+            assert e.value.code == bd.EINVAL
+        for bad in ((4, 1, 1, 1), (bd.KERNEL_GEMM, 7, 1, 1), (bd.KERNEL_GEMM, 8, 1, 3),
+                    (bd.KERNEL_ROWS16, 1, 1, 16)):
+            with pytest.raises(bd.BoostError) as e:
+                bd.boost_gemv_set_route(ctx, *bad)
+            assert e.value.code == bd.EINVAL
+    finally:
+        bd.boost_shutdown(ctx)

@@ -170,17 +170,12 @@ def test_placement_invariance_and_parity(gpu_ctx, N, K, B):
                                    (1000, 8, 100), (600, 4096, 128), (300, 14336, 128),
                                    (130, 14336, 256), (40, 56, 200)])
 def test_mfma_placement_invariance_and_parity(gpu_ctx, N, K, B):
-    """Batches from 7 up run on the matrix cores: bitwise-equal y under every
-    map and schedule, every result within the bar of the oracle (ragged
-    batch tiles, rows cut by page boundaries, pages of both tiers).  Up to
-    B = 16 one batch tile with weights staged through LDS, in one row tile
-    or (B = 12 on a matrix of 2^25 elements) two.  From B = 17 the GEMM
-    covers 2, 4, 8 and 16 batch tiles with 64-row units (B = 20, 33, 64,
-    100, 128, 200) and 128-row units (K = 14336 at B = 64, 128 and 256, on
-    eight wavefronts), each with its own wavefront grid, and the host pages
-    of the "host", "alt" and "mpp3" maps run as 16-row sub-units: the
-    bitwise comparison across maps checks that they sum in the same
-    order."""
+    """The matrix cores as planned (16-row kernel or GEMM), at 1, 2, 4, 8 and
+    16 batch tiles: bitwise-equal y under every map and schedule and any number
+    of host workers, every result within the bar of the oracle (ragged batch
+    tiles, rows cut by page boundaries, pages of both tiers; host pages of the
+    GEMM run as 16-row sub-units that must sum in the units' order).  Each unit
+    of the GEMM by itself: test_gemm_units_invariance_and_parity."""
     w, x = synth.gemv_inputs(17 + N + K + B, N, K, B)
     n = opl.n_pages(w.nbytes)
     maps = {"hbm": np.zeros(n, np.uint8), "host": np.ones(n, np.uint8),
@@ -208,20 +203,45 @@ def test_mfma_placement_invariance_and_parity(gpu_ctx, N, K, B):
         assert np.array_equal(y.view(np.uint32), outs[0].view(np.uint32))
 
 
-# One shape for every unit of the matrix-core GEMM and every edge of its
-# dispatch: units of several pages whose count is no multiple of theirs and
-# whose pages lie on both tiers (23096 and 28672 columns: four, 13696: two),
-# 1, 2, 4, 5 and 8 row tiles a page, rows that share cache lines (K % 64), slices
-# with a ragged last stage, N % 4 != 0 (single stores), both sides of the
-# few-rows kernel and of the GEMV's batch range.
-@pytest.mark.parametrize("N,K,B", [(230, 23096, 20), (190, 28672, 130), (420, 13696, 33),
-                                   (1300, 5000, 4), (1200, 3000, 4), (1201, 3000, 16),
-                                   (901, 9000, 16), (2304, 5120, 64), (640, 8192, 17),
-                                   (3000, 1032, 5), (77, 14336, 65), (6000, 72, 40)])
-def test_gemm_units_invariance_and_parity(gpu_ctx, N, K, B):
-    """Every unit shape of the matrix-core GEMM: the fp32 summation bound
-    against the oracle, and the same bits under all-HBM, alternating, modulo
-    and all-host maps and under both schedules."""
+# Sizes at which each GEMM unit has something to go wrong: several pages whose
+# count is no multiple of the unit's, the last of them short; rows cut by every
+# page boundary and (3080, 5000) rows that share cache lines (K % 64); odd and
+# even N (single stores); units that the last rows of a page do not fill.
+UNITS = {(8, 2): [(560, 8328, 2), (515, 8192, 1)], (3, 4): [(230, 23096, 4), (133, 28672, 1)],
+         (8, 1): [(1301, 5000, 1), (700, 14336, 4)], (5, 1): [(1301, 5000, 2), (300, 14336, 1)],
+         (4, 1): [(1003, 3080, 2), (300, 14336, 8)], (2, 1): [(1003, 3080, 1), (6000, 72, 1)],
+         (1, 1): [(1003, 3080, 4), (77, 14336, 1)]}
+
+
+@pytest.mark.parametrize("B", [2, 20, 49, 100, 250])
+@pytest.mark.parametrize("unit", sorted(UNITS))
+def test_gemm_units_invariance_and_parity(gpu_ctx, unit, B):
+    """Every unit of the GEMM at every number of batch tiles (each a wavefront
+    grid and rings of its own), set rather than planned: the fp32 summation
+    bound against the oracle, and the same bits under all-HBM, alternating,
+    modulo, irregular and all-host maps and under both schedules."""
+    if unit == (1, 1) and B > 32:
+        bd.boost_gemv_set_route(gpu_ctx, bd.KERNEL_GEMM, 1, 1, 1)
+        w, x = synth.gemv_inputs(1, 64, 512, B)
+        t = place(gpu_ctx, w, M=2)
+        try:
+            with pytest.raises(bd.BoostError) as e:  # refused, not run
+                run_gemv(gpu_ctx, t, 64, 512, to_dev_u16(x), B)
+            assert e.value.code == bd.EINVAL
+        finally:
+            bd.boost_gemv_set_route(gpu_ctx, bd.KERNEL_AUTO)
+            bd.boost_tensor_free(t)
+        return
+    for N, K, S in UNITS[unit]:
+        check_route(gpu_ctx, (bd.KERNEL_GEMM, *unit, S), N, K, B)
+
+
+@pytest.mark.parametrize("N,K,B,S", [(1003, 3080, 4, 4), (300, 14336, 16, 1), (77, 28672, 9, 8)])
+def test_rows16_invariance_and_parity(gpu_ctx, N, K, B, S):
+    check_route(gpu_ctx, (bd.KERNEL_ROWS16, 1, 1, S), N, K, B)
+
+
+def check_route(ctx, route, N, K, B):
     w, x = synth.gemv_inputs(17 * N + K + B, N, K, B)
     n = opl.n_pages(w.nbytes)
     maps = {"hbm": np.zeros(n, np.uint8), "alt": (np.arange(n) % 2).astype(np.uint8),
@@ -229,21 +249,26 @@ def test_gemm_units_invariance_and_parity(gpu_ctx, N, K, B):
             "host": np.ones(n, np.uint8)}
     xd = to_dev_u16(x)
     first = None
-    for name, tiers in maps.items():
-        t = place(gpu_ctx, w, tiers=tiers)
-        try:
-            for sched in (bd.SCHED_CAP, bd.SCHED_ADDRESS):
-                bd.boost_gemv_set_schedule(gpu_ctx, sched, 0)
-                y = run_gemv(gpu_ctx, t, N, K, xd, B)
-                if first is None:
-                    first = y
-                    assert_f32_bound(y, w, x)
-                    yb = run_gemv(gpu_ctx, t, N, K, xd, B, bd.DTYPE_BF16)
-                    assert np.array_equal(yb, og.f32_to_bf16(y))
-                assert np.array_equal(y.view(np.uint32), first.view(np.uint32)), (name, sched)
-        finally:
-            bd.boost_gemv_set_schedule(gpu_ctx, bd.SCHED_CAP, 0)
-            bd.boost_tensor_free(t)
+    try:
+        bd.boost_gemv_set_route(ctx, *route)
+        for name, tiers in maps.items():
+            t = place(ctx, w, tiers=tiers)
+            try:
+                for sched in (bd.SCHED_CAP, bd.SCHED_ADDRESS):
+                    bd.boost_gemv_set_schedule(ctx, sched, 0)
+                    y = run_gemv(ctx, t, N, K, xd, B)
+                    if first is None:
+                        first = y
+                        assert_f32_bound(y, w, x)
+                        yb = run_gemv(ctx, t, N, K, xd, B, bd.DTYPE_BF16)
+                        assert np.array_equal(yb, og.f32_to_bf16(y))
+                    assert np.array_equal(y.view(np.uint32), first.view(np.uint32)), \
+                        (N, K, name, sched)
+            finally:
+                bd.boost_tensor_free(t)
+    finally:
+        bd.boost_gemv_set_schedule(ctx, bd.SCHED_CAP, 0)
+        bd.boost_gemv_set_route(ctx, bd.KERNEL_AUTO)
 
 
 @pytest.mark.parametrize("B", [9, 16, 256])
@@ -382,9 +407,8 @@ def test_full_size_70b_tensor_sampled_batch8(gpu_ctx, kind):
     """Full-size Llama-3-70B-shaped tensors (fused qkv 10240 x 8192, o
     8192 x 8192, fused gate_up 57344 x 8192, down 8192 x 28672, lm_head
     128256 x 8192: 80 to 1002 pages) placed by MPP at M = 6, the modulus of
-    the 120e9-byte HBM weight budget, at batch 8: the matrix-core kernel with
-    weights staged through LDS, one K slice, many host units per CAP worker,
-    and (down) rows cut by page boundaries through split_fixup.  Sampled rows,
+    the 120e9-byte HBM weight budget, at batch 8: the GEMM with many host units
+    per CAP worker and (down) rows cut by page boundaries.  Sampled rows,
     including every row a page boundary cuts, element by element against the
     oracle at the stated bar and within the fp32 summation bound."""
     import torch
