@@ -235,21 +235,44 @@ def ab_pairs(torch, fn_a, fn_b, pairs):
             "speedup_of_medians": round(float(np.median(tb) / np.median(ta)), 5)}
 
 
+def source_hashes(source: str):
+    """What a counter summary is keyed on: the hash of a kernel's source file and
+    that of the csrc headers that it includes, itself or through others."""
+    import hashlib
+    import re
+    csrc = os.path.join(ROOT, "paper_2609_13592_amd", "csrc")
+
+    def read(name):
+        with open(os.path.join(csrc, name), "rb") as fh:
+            return fh.read()
+
+    found, todo = {}, [source]
+    while todo:
+        name = todo.pop()
+        if name not in found:
+            found[name] = read(name)
+            todo += [h for h in re.findall(r'^#include "([^"]+)"', found[name].decode(), re.M)
+                     if os.path.exists(os.path.join(csrc, h))]
+    src = found.pop(source)
+    return {"source_sha256": hashlib.sha256(src).hexdigest(),
+            "headers_sha256": hashlib.sha256(b"".join(found[n] for n in sorted(found))).hexdigest()}
+
+
+def current_counters(entry, source: str) -> bool:
+    """Whether the counters of `entry` were taken on the sources as they are."""
+    return all(entry.get(k) == v for k, v in source_hashes(source).items())
+
+
 def tier_counter_entry(part: str):
     """The committed counter summary of one tiered call of `part` (chain step,
     single layer, config-3 attention) from profiles/tier_counters.json, or
-    None when the kernel source changed since the counters were taken."""
-    import hashlib
+    None when the kernel's sources changed since the counters were taken."""
     path = os.path.join(ROOT, "profiles", "tier_counters.json")
     try:
         ent = json.load(open(path))[part]
-        src = open(os.path.join(ROOT, "paper_2609_13592_amd", "csrc", ent["source"]),
-                   "rb").read()
+        return ent if current_counters(ent, ent["source"]) else None
     except (OSError, KeyError, ValueError):
         return None
-    if hashlib.sha256(src).hexdigest() != ent["source_sha256"]:
-        return None
-    return ent
 
 
 def per_tier(part, ms, placement_hbm, placement_host, modulus=None):
@@ -403,16 +426,14 @@ def attention_bench(bd, ctx, torch, M, steps, warmup):
 # ------------------------------------------------------------ traffic data
 def counter_traffic(kernel: str, source: str):
     """HBM bytes per launch from the committed FETCH_SIZE / WRITE_SIZE summary
-    (profiles/traffic_counters.json), or None when the kernel source changed
+    (profiles/traffic_counters.json), or None when the kernel's sources changed
     since the counters were taken."""
-    import hashlib
     path = os.path.join(ROOT, "profiles", "traffic_counters.json")
     try:
         data = json.load(open(path))[kernel]
-        src = open(os.path.join(ROOT, "paper_2609_13592_amd", "csrc", source), "rb").read()
+        if not current_counters(data, source):
+            return None
     except (OSError, KeyError, ValueError):
-        return None
-    if hashlib.sha256(src).hexdigest() != data["source_sha256"]:
         return None
     return int(data["traffic_bytes_per_launch"])
 
@@ -492,7 +513,6 @@ def write_traffic_profile(dirs: str, out_dir: str = ""):
     (the 128 layer launches by grid, the head's tiered launch as the largest
     gemv grid not in the layers) and one config-3 attention call (partition
     and merge kernels).  Written to profiles/traffic_counters.json."""
-    import hashlib
     fetch_dir, write_dir = dirs.split(",")
     f, w = summarize_pmc(fetch_dir), summarize_pmc(write_dir)
 
@@ -559,14 +579,11 @@ def write_traffic_profile(dirs: str, out_dir: str = ""):
             if key.startswith(kname):
                 attn_w += ent["per_dispatch"].get("WRITE_SIZE", 0.0) * 1024 * wscale
 
-    def sha(src):
-        return hashlib.sha256(open(os.path.join(ROOT, "paper_2609_13592_amd", "csrc", src),
-                                   "rb").read()).hexdigest()
-    prof = {"gemv": {"source_sha256": sha("gemv.hip"),
+    prof = {"gemv": {**source_hashes("gemv.hip"),
                      "traffic_bytes_per_launch": int((fsum + wsum) / launches),
                      "fetch_bytes_per_step": int(fsum), "write_bytes_per_step": int(wsum),
                      "launches_per_step": launches},
-            "attn_partition": {"source_sha256": sha("attn.hip"),
+            "attn_partition": {**source_hashes("attn.hip"),
                                "traffic_bytes_per_launch": int(attn_f + attn_w),
                                "fetch_bytes": int(attn_f), "write_bytes": int(attn_w)},
             "fetch_scale": round(fscale, 4), "write_scale": round(wscale, 4)}
@@ -588,8 +605,7 @@ TIER_KERNELS = {"chain": (("gemv_kernel", "split_fixup"), "gemv.hip"),
 def write_tier_profile(directory: str, out_dir: str = ""):
     """Per-tier bytes of the tiered calls of a tier_counters run, summed over
     the part's kernels, against the placement's bytes; written to
-    profiles/tier_counters.json with the kernel source's hash."""
-    import hashlib
+    profiles/tier_counters.json with the hashes of the kernel's sources."""
     prof = {}
     lines = ["| part | modulus | kernels | DRAM bytes (counter) | host bytes (counter) | "
              "HBM bytes (placement) | host bytes (placement) | DRAM / placement | "
@@ -613,9 +629,7 @@ def write_tier_profile(directory: str, out_dir: str = ""):
             hbm_p = meta["kv_bytes"] - host_p
         else:
             hbm_p, host_p = meta["weight_hbm_bytes"], meta["weight_host_bytes"]
-        sha = hashlib.sha256(open(os.path.join(ROOT, "paper_2609_13592_amd", "csrc", source),
-                                  "rb").read()).hexdigest()
-        prof[part] = {"source": source, "source_sha256": sha, "modulus": meta["modulus"],
+        prof[part] = {"source": source, **source_hashes(source), "modulus": meta["modulus"],
                       "hbm_bytes": int(round(dram)), "host_bytes": int(round(io)),
                       "placement_hbm_bytes": int(hbm_p), "placement_host_bytes": int(host_p),
                       "hbm_over_placement": round(dram / hbm_p, 5),

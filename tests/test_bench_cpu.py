@@ -6,6 +6,7 @@ import csv
 import hashlib
 import json
 import os
+import shutil
 import sys
 
 import pytest
@@ -97,6 +98,28 @@ def test_tier_profile_and_lookup(tmp_path, monkeypatch):
     monkeypatch.setattr(bench, "tier_counter_entry", lambda part: None)
     bare = bench.per_tier("chain", 2.0, 1000, 10, 126)
     assert bare["bytes_from"] == "placement" and bare["hbm_gbps"] == round(1000 / 2e-3 / 1e9, 1)
+
+
+def test_counters_are_dropped_when_a_header_changes(tmp_path, monkeypatch):
+    """A kernel's counters are those of its source and of every header that it
+    includes: a change in either drops them."""
+    csrc = tmp_path / "paper_2609_13592_amd" / "csrc"
+    shutil.copytree(os.path.join(ROOT, "paper_2609_13592_amd", "csrc"), csrc)
+    (tmp_path / "profiles").mkdir()
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    ent = {**bench.source_hashes("gemv.hip"), "traffic_bytes_per_launch": 5}
+    (tmp_path / "profiles" / "traffic_counters.json").write_text(json.dumps({"gemv": ent}))
+    (tmp_path / "profiles" / "tier_counters.json").write_text(
+        json.dumps({"chain": {**ent, "source": "gemv.hip"}}))
+    assert bench.counter_traffic("gemv", "gemv.hip") == 5
+    assert bench.tier_counter_entry("chain")["traffic_bytes_per_launch"] == 5
+    for name in ("gemv_common.h", "runtime.h"):  # included, and included by that
+        kept = (csrc / name).read_text()
+        (csrc / name).write_text(kept + "\n")
+        assert bench.counter_traffic("gemv", "gemv.hip") is None
+        assert bench.tier_counter_entry("chain") is None
+        (csrc / name).write_text(kept)
+    assert bench.counter_traffic("gemv", "gemv.hip") == 5
 
 
 def test_traffic_profile_scales_by_references(tmp_path):
