@@ -36,6 +36,7 @@
 // two pages of 8192 columns (57344 x 8192, 256 rows: 257 us, 287 with one
 // page), four of 28672 (8192 x 28672, 64 rows: 85 us; 131 with 64-row units).
 #include <algorithm>
+#include <type_traits>
 
 #include "gemm_plan.h"
 #include "gemv_common.h"
@@ -60,6 +61,9 @@ constexpr int dma_wave_grid() {
     }
   return best;
 }
+// Whether a wavefront of `tiles` 16 x 16 tiles keeps its sums in blocks: a
+// second set of sums, for which 24 and 32 tiles leave no registers.
+constexpr bool gemm_block_sums(int tiles) { return tiles <= 16; }
 template <int BT, int RTL, int G, int NW>
 struct GemmCfg {
   static constexpr int kWStage = 2 * G * RTL * kDmaBlk, kXStage = 2 * BT * kDmaBlk;
@@ -67,6 +71,9 @@ struct GemmCfg {
   static constexpr int kWRing = kWs * kWStage, kXRing = kXs * kXStage;
   static constexpr int kGrid = dma_wave_grid<BT, RTL, G, NW>();
   static constexpr int WR = kGrid / 16, WB = kGrid % 16;
+  // sums in blocks, in the unit and, the same order being owed, in its host
+  // sub-units
+  static constexpr bool kBlocks = gemm_block_sums(G * RTL / WR * (BT / WB));
   // batch groups of a host sub-unit (one row tile)
   static constexpr int kHostWB = BT < NW ? BT : NW;
   static_assert(kGrid > 0 && kWs >= 2, "no wavefront grid or ring fits the unit");
@@ -321,6 +328,39 @@ __device__ __forceinline__ void gemm_dma_unit(const GemvParams& P, int page_in, 
       for (int a = 0; a < RW; ++a)
         acc[a][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.w[a], f.x[t], acc[a][t], 0, 0, 0);
   };
+  // Sums in blocks of `block` stages (a power of two): the running sums of a
+  // block are added to `sum` and begun anew, since one chain over a long slice
+  // rounds at the size of the whole sum at every step (8192 x 28672 at 8 rows:
+  // relative error 7.5e-7 as one chain).  Eight blocks a slice, of 512 columns
+  // at least: with sqrt(n) blocks of the n steps, sums of 64 columns err half
+  // as much and cost 4-6 % of the time at 17 rows and more, these 1 %.  One
+  // batch tile (two or three tiles a wavefront) adds every stage to sums of 64
+  // bits, so that the error does not grow with K at all: the GEMV, which takes
+  // the smaller batches, sums over 64 lanes and errs no more (4096 columns:
+  // 9e-8; 6.5e-8 here).  That costs 1 %.
+  constexpr bool kBlocks = C::kBlocks, kWide = BT == 1;
+  using sum_t = typename std::conditional<kWide, f64x4_t, f32x4_t>::type;
+  sum_t sum[kBlocks ? RW : 1][kBlocks ? BW : 1];
+  if constexpr (kBlocks) {
+#pragma unroll
+    for (int a = 0; a < RW; ++a)
+#pragma unroll
+      for (int t = 0; t < BW; ++t) sum[a][t] = sum_t(0.f);
+  }
+  auto close_block = [&] {
+    if constexpr (kBlocks) {
+#pragma unroll
+      for (int a = 0; a < RW; ++a)
+#pragma unroll
+        for (int t = 0; t < BW; ++t) {
+          sum[a][t] += __builtin_convertvector(acc[a][t], sum_t);
+          acc[a][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+  };
+  int block = 8;
+  while (8 * block < nst) block *= 2;
+  if (!kBlocks || kWide) block = nst;
 
   // A stage is two 32-column steps; the fragments of a step are read while
   // the matrix cores work on the step before it (two register sets), and the
@@ -336,27 +376,45 @@ __device__ __forceinline__ void gemm_dma_unit(const GemvParams& P, int page_in, 
   int stage = rot;  // the stage being multiplied
   int used = 0;     // ring slots of this wavefront's operand used up
   if (computes) read(f0, ws, xs, 0, stage);
+  // (blocks in a loop around the stages': a condition among them cost the small
+  // units up to 14 %)
 #pragma unroll 1
-  for (int s = 0; s < nst; ++s) {
-    if (computes) {
-      read(f1, ws, xs, 1, stage);
+  for (int s0 = 0; s0 < nst; s0 += block) {
+    const int s1 = min(nst, s0 + block);
+#pragma unroll 1
+    for (int s = s0; s < s1; ++s) {
+      if (computes) {
+        read(f1, ws, xs, 1, stage);
+        __builtin_amdgcn_sched_barrier(0);
+        mma(f0);
+      }
       __builtin_amdgcn_sched_barrier(0);
-      mma(f0);
+      ++stage;
+      // whether W's next stage is in its next slot, and this operand's
+      const bool w_next = !HOST || stage % kSpan == 0 || stage == nst, next = w_next || !wl;
+      stage = stage == nst ? 0 : stage;
+      if (next) landed(min(depth, loads - used) - 2);
+      __syncthreads();
+      if (w_next) ws = ws + kWStage == kWRing ? 0 : ws + kWStage;
+      xs = xs + C::kXStage == C::kXRing ? 0 : xs + C::kXStage;
+      if (computes) read(f0, ws, xs, 0, stage);  // (after the last stage: not used)
+      if (next && used + depth < loads) issue();
+      used += next;
+      __builtin_amdgcn_sched_barrier(0);
+      if (computes) {
+        if (kWide) close_block();  // (the products of f0 have had the barrier's wait)
+        mma(f1);
+      }
     }
-    __builtin_amdgcn_sched_barrier(0);
-    ++stage;
-    // whether W's next stage is in its next slot, and this operand's
-    const bool w_next = !HOST || stage % kSpan == 0 || stage == nst, next = w_next || !wl;
-    stage = stage == nst ? 0 : stage;
-    if (next) landed(min(depth, loads - used) - 2);
-    __syncthreads();
-    if (w_next) ws = ws + kWStage == kWRing ? 0 : ws + kWStage;
-    xs = xs + C::kXStage == C::kXRing ? 0 : xs + C::kXStage;
-    if (computes) read(f0, ws, xs, 0, stage);  // (after the last stage: not used)
-    if (next && used + depth < loads) issue();
-    used += next;
-    __builtin_amdgcn_sched_barrier(0);
-    if (computes) mma(f1);
+    if (!kWide && computes) close_block();
+  }
+  if constexpr (kBlocks) {
+#pragma unroll
+    for (int a = 0; a < RW; ++a)
+#pragma unroll
+      for (int t = 0; t < BW; ++t)
+        acc[a][t] = __builtin_convertvector(
+            sum[a][t] + __builtin_convertvector(acc[a][t], sum_t), f32x4_t);
   }
   __syncthreads();  // LDS is reused by the next unit of a persistent worker
 

@@ -307,7 +307,7 @@ __global__ __launch_bounds__(256) void split_fixup(GemvParams P, int n_pages, in
 // ---------------------------------------------------------------------------
 // Matrices of few rows at up to 16 batch rows: one 16-row tile of a page and
 // one K slice per workgroup, the slice split over its four wavefronts and
-// their partial tiles summed in LDS in wavefront order.  The GEMM of gemm.h
+// their partial tiles summed in LDS in wavefront order, in 64 bits.  The GEMM of gemm.h
 // has too few units there, each a long chain of stages (534 x 19232, B = 15:
 // 14.6 us here, 17.6 us there; 1160 x 15224, B = 9: 17.3 and 20.6); with more
 // rows it is the faster one (1250 x 4656, B = 7: 11.2 us here, 10.4 there;
@@ -323,6 +323,7 @@ __global__ __launch_bounds__(256) void split_fixup(GemvParams P, int n_pages, in
 constexpr int kMfmaCols = 256;                          // columns per chunk
 constexpr int kMfmaTileFloats = 16 * kMfmaCols * 2 / 4;  // one wavefront's tile
 constexpr int kMfmaSumFloats = 16 * 17;                 // [batch][row], padded
+constexpr int kMfmaSums = kWaves * kMfmaSumFloats;      // of every wavefront
 
 __device__ void mfma_unit(const GemvParams& P, int page, int unit, float* lds) {
   const int j = unit / P.S, slice = unit % P.S;
@@ -343,7 +344,8 @@ __device__ void mfma_unit(const GemvParams& P, int page, int unit, float* lds) {
   const __amdgpu_buffer_rsrc_t xr =
       make_rsrc(P.x, static_cast<uint32_t>(static_cast<int64_t>(P.B) * K * 2));
   const uint32_t xo = lrow < P.B ? static_cast<uint32_t>(lrow * K * 2) : kOOB;
-  f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+  // sums of two steps, added up in 64 bits (as the GEMM's one batch tile)
+  f64x4_t sum = {0., 0., 0., 0.};
 
   constexpr int kStep = 32;
   // this unit's K slice, then this wavefront's quarter of it
@@ -355,7 +357,7 @@ __device__ void mfma_unit(const GemvParams& P, int page, int unit, float* lds) {
   const int64_t k_beg = min(s_end, s_beg + wave * kper);
   const int64_t k_end = min(s_end, k_beg + kper);
 
-  uint4* tile = reinterpret_cast<uint4*>(lds + kMfmaSumFloats + wave * kMfmaTileFloats);
+  uint4* tile = reinterpret_cast<uint4*>(lds + kMfmaSums + wave * kMfmaTileFloats);
   // load instruction i: rows 2i and 2i+1 (lanes 0-31 / 32-63), 16 bytes each;
   // a row begun on the previous page gets a wrapped (huge) offset, so its
   // columns before the page read as zero
@@ -394,33 +396,33 @@ __device__ void mfma_unit(const GemvParams& P, int page, int unit, float* lds) {
     }
     load_chunk(kb + kMfmaCols);
     __builtin_amdgcn_sched_barrier(0);
+    f32x4_t acc[kChunkSteps / 2];
 #pragma unroll
     for (int st = 0; st < kChunkSteps; ++st) {
       const uint4 a = tile[lrow * 32 + ((4 * st + lgrp) ^ lrow)];
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a),
-                                                    __builtin_bit_cast(bf16x8_t, xv[st]), acc, 0,
-                                                    0, 0);
+      const f32x4_t c = st % 2 ? acc[st / 2] : f32x4_t{0.f, 0.f, 0.f, 0.f};
+      acc[st / 2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+          __builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, xv[st]), c, 0, 0, 0);
     }
+#pragma unroll
+    for (int st = 0; st < kChunkSteps / 2; ++st)
+      sum += __builtin_convertvector(acc[st], f64x4_t);
   }
 
-  // output element (row 4 lgrp + e, batch row lrow); LDS holds the unit's
-  // [batch][row] tile, summed over wavefronts in order
-#pragma unroll 1
-  for (int w = 0; w < kWaves; ++w) {
-    if (wave == w) {
+  // output element (row 4 lgrp + e, batch row lrow); LDS holds the [batch][row]
+  // tile of every wavefront, added up in wavefront order and rounded once
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        float* q = lds + lrow * 17 + 4 * lgrp + e;
-        *q = w == 0 ? acc[e] : *q + acc[e];
-      }
-    }
-    __syncthreads();
-  }
+  for (int e = 0; e < 4; ++e)
+    lds[wave * kMfmaSumFloats + lrow * 17 + 4 * lgrp + e] = static_cast<float>(sum[e]);
+  __syncthreads();
   static_assert(kThreads == 16 * 16, "one output per thread");
   const int b = threadIdx.x / 16, i = threadIdx.x % 16;
   const int64_t r = rbase + i;
   if (b < P.B && r <= r_hi) {
-    const float v = lds[b * 17 + i];
+    double all = 0.;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) all += lds[w * kMfmaSumFloats + b * 17 + i];
+    const float v = static_cast<float>(all);
     const int64_t e0 = r * K;
     const int side = e0 < pe0 ? 1 : (e0 + K > pe1 ? 0 : -1);  // cut row: its part's side
     const int64_t bnd = side == 1 ? page : page + 1;
@@ -437,7 +439,7 @@ __device__ void mfma_unit(const GemvParams& P, int page, int unit, float* lds) {
 }
 
 __global__ __launch_bounds__(kThreads) void mfma_kernel(GemvParams P) {
-  __shared__ float lds[kMfmaSumFloats + kWaves * kMfmaTileFloats];
+  __shared__ float lds[kMfmaSums + kWaves * kMfmaTileFloats];
   const int bid = blockIdx.x;
   const int U = P.units_per_page;
   if (P.address_order) {

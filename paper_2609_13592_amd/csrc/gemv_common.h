@@ -130,6 +130,7 @@ constexpr uint32_t kOOB = 0x80000000u;
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+typedef __attribute__((ext_vector_type(4))) double f64x4_t;
 
 // Host side of a launch (gemv.hip).
 // Rows of the matrix that the page with the most of them meets.

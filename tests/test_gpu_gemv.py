@@ -271,6 +271,30 @@ def check_route(ctx, route, N, K, B):
         bd.boost_gemv_set_route(ctx, bd.KERNEL_AUTO)
 
 
+# (GEMM units whose wavefronts hold 1, 4, 8 and 16 tiles; one slice)
+@pytest.mark.parametrize("unit,B", [((2, 1), 8), ((4, 1), 32), ((8, 1), 100), ((8, 1), 256)])
+def test_gemm_sums_error(gpu_ctx, unit, B):
+    """The sums of long rows are added up in blocks.  One chain of n = K / 32
+    products errs by about c sqrt(n / 2) of the result, eight blocks by
+    c sqrt(n / 16 + 4), with c = 3.5e-8, the root mean square of what rounding to
+    24 bits loses: 7.9e-7 and 2.9e-7 at K = 32768.  The line between them is drawn
+    at 4.5e-7, root mean square over all results; one batch tile, in 64 bits, is
+    held to 1e-7 (a product of 64 columns and the last rounding: 1.5 c)."""
+    N, K = 96, 32768
+    w, x = synth.gemv_inputs(unit[0] + B, N, K, B)
+    t = place(gpu_ctx, w, M=3)
+    try:
+        bd.boost_gemv_set_route(gpu_ctx, bd.KERNEL_GEMM, *unit, 1)
+        y = run_gemv(gpu_ctx, t, N, K, to_dev_u16(x), B)
+    finally:
+        bd.boost_gemv_set_route(gpu_ctx, bd.KERNEL_AUTO)
+        bd.boost_tensor_free(t)
+    ref = og.bf16_to_f32(x).astype(np.float64) @ og.bf16_to_f32(w).astype(np.float64).T
+    err = np.sqrt(np.mean((y - ref) ** 2) / np.mean(ref ** 2))
+    print(f"unit {unit} B {B}: {err:.2e}")
+    assert err < (1e-7 if B <= 16 else 4.5e-7)
+
+
 @pytest.mark.parametrize("B", [9, 16, 256])
 def test_mfma_exact_pins(gpu_ctx, B):
     """W = I gives x back exactly on the matrix-core path; bf16 output of it
