@@ -337,8 +337,7 @@ int boost_gemv_route(const boost_ctx *ctx, int N, int K, int B, int max_slices,
  * bf16 rounded to nearest even (BOOST_DTYPE_BF16).  Accumulation is fp32 and
  * the reduction order is fixed, so results are bitwise reproducible and do
  * not depend on the placement or the schedule.  1 <= B <= 256, K % 8 == 0,
- * N >= 1.  Batches up to 3 (1 on matrices of 2^26 elements or
- * more) run as a GEMV on the vector units; larger ones as a
+ * N >= 1.  Batches up to 3 run as a GEMV on the vector units; larger ones as a
  * skinny GEMM on the matrix cores (the batch sizes of §5.10), with
  * the same page-confined work units; a matrix too small to fill the GPU at a
  * large batch has K split over several workgroups whose partials go to a

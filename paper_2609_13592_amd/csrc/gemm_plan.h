@@ -142,16 +142,14 @@ inline Route plan_few_rows(const PlanInput& in) {
 
 // Whether a call runs on the matrix cores (the others on the GEMV): from four
 // batch rows (28672 x 4096 at 4 / 6 rows: 38.1 / 38.1 us against 43.6 / 50.1;
-// 4096 x 4096 at 6: 10.9 against 15.5; 5003 x 3080 at 4: 16.4 against 17.3),
-// and at two and three on matrices of 2^26 elements or more (28672 x 4096 at
-// 2: 38.2 against 41.8 us, 8192 x 28672: 76.4 against 82.6; smaller ones lose
-// to the split sums' launch, 5003 x 3080 at 2: 17.3 against 11.3).
-inline bool matrix_cores(int N, int K, int B) {
-  return B >= 4 || (B >= 2 && static_cast<int64_t>(N) * K >= (int64_t{1} << 26));
-}
+// 4096 x 4096 at 6: 10.9 against 15.5; 5003 x 3080 at 4: 16.4 against 17.3).
+// Of 70 drawn matrices of 2^26 elements or more at two and three rows 59 take 3 %
+// longer on them or more (49158 x 1976 at 3: 57.8 us against 40.8; 22400 x 7040
+// at 2: 81.9 and 57.9), a few less (28672 x 4096 at 2: 38.2 and 41.8).
+inline bool matrix_cores(int B) { return B >= 4; }
 
 inline Route plan(const PlanInput& in) {
-  if (!matrix_cores(in.N, in.K, in.B)) return {kGemv, 0, 1};
+  if (!matrix_cores(in.B)) return {kGemv, 0, 1};
   if (in.B <= 16 && in.N <= kFewRows) return plan_few_rows(in);
   return plan_gemm(in);
 }

@@ -234,3 +234,15 @@ def test_gemv_route_query():
             assert e.value.code == bd.EINVAL
     finally:
         bd.boost_shutdown(ctx)
+
+
+@pytest.mark.parametrize("N,K", [(49158, 1976), (22400, 7040), (28672, 4096), (300, 28672), (1, 8)])
+def test_two_and_three_rows_take_the_gemv(N, K):
+    """Measured: most matrices of any size take longer on the matrix cores."""
+    ctx = bd.boost_init(-1)
+    try:
+        for B in (1, 2, 3):
+            assert bd.boost_gemv_route(ctx, N, K, B) == (bd.KERNEL_GEMV, 0, 0, 1)
+        assert bd.boost_gemv_route(ctx, N, K, 4)[0] != bd.KERNEL_GEMV
+    finally:
+        bd.boost_shutdown(ctx)
