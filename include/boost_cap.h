@@ -302,10 +302,11 @@ int boost_prefetch(boost_ctx *ctx, const boost_tensor *view, void *stream);
  *     workgroups, dispatched first, stream every host-page unit while all
  *     other workgroups stream HBM-page units, so host and HBM reads overlap in
  *     every wave (§3 "CAP").  host_workers = 0 picks the default: n_cu / 16
- *     for the GEMV; for the matrix-core kernels one worker per 16
- *     host units of the tensor, at least n_cu / 16 and at most n_cu / 8
- *     (a host unit is one 16-row tile of a page, so a host page spreads over
- *     more workers).  Never more workers than host units. */
+ *     for the GEMV; for the matrix-core kernels, whose host unit is one 16-row
+ *     tile of a page (and one K slice), as many as spread the host units evenly
+ *     over the fewest rounds that n_cu / 8 workers allow (100 units on 256
+ *     compute units: 25 workers, four units each), at least n_cu / 16.  Never
+ *     more workers than host units. */
 #define BOOST_SCHED_ADDRESS 0
 #define BOOST_SCHED_CAP 1
 int boost_gemv_set_schedule(boost_ctx *ctx, int schedule, int host_workers);
@@ -313,10 +314,10 @@ int boost_gemv_set_schedule(boost_ctx *ctx, int schedule, int host_workers);
 /* The kernel of a decode GEMV call and how it is cut.  Planned from the sizes
  * (BOOST_KERNEL_AUTO), or set for every later call on a context so that tests
  * and measurements reach each one at any size: the GEMV (up to 3 batch rows),
- * the kernel of 16-row units (up to 16), or the GEMM with units of `row_tiles`
- * 16-row tiles of each of `pages` consecutive pages (8 x 1, 8 x 2, 3 x 4,
- * 5 x 1, 4 x 1, 2 x 1, 1 x 1; several pages only where no page meets more rows
- * than that, 1 x 1 up to 32 batch rows), with K cut into `slices` (1, 2, 4 or
+ * the kernel of one or two 16-row tiles a unit (up to 16), or the GEMM with
+ * units of `row_tiles` 16-row tiles of each of `pages` consecutive pages (8 x 1,
+ * 8 x 2, 3 x 4, 5 x 1, 4 x 1, 2 x 1; several pages only where no page meets more
+ * rows than that), with K cut into `slices` (1, 2, 4 or
  * 8; those of fewer than 512 columns, or more than the workspace holds, do not
  * fit).  A call that does not fit what is set fails with EINVAL. */
 #define BOOST_KERNEL_AUTO 0
@@ -337,10 +338,14 @@ int boost_gemv_route(const boost_ctx *ctx, int N, int K, int B, int max_slices,
  * bf16 rounded to nearest even (BOOST_DTYPE_BF16).  Accumulation is fp32 and
  * the reduction order is fixed, so results are bitwise reproducible and do
  * not depend on the placement or the schedule.  1 <= B <= 256, K % 8 == 0,
- * N >= 1.  Batches up to 3 run as a GEMV on the vector units; larger ones as a
- * skinny GEMM on the matrix cores (the batch sizes of §5.10), with
- * the same page-confined work units; a matrix too small to fill the GPU at a
- * large batch has K split over several workgroups whose partials go to a
+ * N >= 1.  Batches up to 3 run as a GEMV on the vector units, larger ones
+ * (the batch sizes of §5.10) on the matrix cores: up to 16 rows a kernel of
+ * 16-row units or, as larger ones, a skinny GEMM, by the sizes.  The GEMM's work
+ * units lie on one page or, where a page holds few rows, on up to four
+ * consecutive ones; under BOOST_SCHED_CAP those of a unit's pages that are on
+ * the host are left to the host workers, so that no workgroup reads both
+ * tiers; in address order (BOOST_SCHED_ADDRESS) one may.  A matrix too small to
+ * fill the GPU has K split over several workgroups whose partials go to a
  * workspace owned by the context (64 MiB, allocated by boost_init) and are
  * summed in slice order by a second kernel.  Calls on one context must
  * therefore be ordered (one stream, or streams joined by events): two
@@ -368,8 +373,8 @@ int boost_decode_gemv(boost_ctx *ctx, const boost_tensor *W, int N, int K,
  * max_slices; it depends only on the shapes, the placement and the context,
  * so it is known on the host when the call returns.
  * It touches no workspace of the context: the partials live in `slices`, and
- * with S == 1 the parts of rows cut between pages of different tiers are
- * staged in a buffer of the tensor W, so calls on different streams may
+ * with S == 1 the parts of cut rows that no one workgroup sums are staged in a
+ * buffer of the tensor W, so calls on different streams may
  * overlap unless they use the same W.
  * 1 <= max_slices <= BOOST_MAX_GEMV_SLICES.  Other arguments and errors as
  * boost_decode_gemv. */

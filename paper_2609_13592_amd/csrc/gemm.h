@@ -519,12 +519,7 @@ int launch_gemm(GemvParams& P, const Route& route, int n_pages, bool need_fixup,
     case 2: return launch_gemm_shape<BT, 3, 4>(P, n_pages, need_fixup, ctx, s);
     case 3: return launch_gemm_shape<BT, 5, 1>(P, n_pages, need_fixup, ctx, s);
     case 4: return launch_gemm_shape<BT, 4, 1>(P, n_pages, need_fixup, ctx, s);
-    case 5: return launch_gemm_shape<BT, 2, 1>(P, n_pages, need_fixup, ctx, s);
-    default:
-      if constexpr (BT <= 2)
-        return launch_gemm_shape<BT, 1, 1>(P, n_pages, need_fixup, ctx, s);
-      else
-        return fail(BOOST_EINVAL, "no unit shape");
+    default: return launch_gemm_shape<BT, 2, 1>(P, n_pages, need_fixup, ctx, s);
   }
 }
 

@@ -51,7 +51,7 @@ constexpr int gemm_occupancy(int bt, int rtl, int g) {
 struct GemmShape {
   int rtl, g;
 };
-constexpr GemmShape kGemmShapes[] = {{8, 1}, {8, 2}, {3, 4}, {5, 1}, {4, 1}, {2, 1}, {1, 1}};
+constexpr GemmShape kGemmShapes[] = {{8, 1}, {8, 2}, {3, 4}, {5, 1}, {4, 1}, {2, 1}};
 constexpr int kNumGemmShapes = sizeof kGemmShapes / sizeof *kGemmShapes;
 
 
@@ -65,11 +65,11 @@ struct PlanInput {
   uint64_t slice_floats;  // of this many floats
 };
 
-enum Kernel { kAuto = 0, kGemv = 1, kFewRowsKernel = 2, kGemm = 3 };
+enum Kernel { kAuto = 0, kGemv = 1, kRows16 = 2, kGemm = 3 };
 
 struct Route {
   int kernel;
-  int shape;  // of kGemmShapes (kGemm)
+  int shape;  // kGemm: index in kGemmShapes; kRows16: row tiles of a unit
   int S;      // K slices
 };
 
@@ -88,83 +88,129 @@ inline uint64_t floats_per_slice(const PlanInput& in) {
   return static_cast<uint64_t>(in.B) * (in.N + 2ull * (in.n_pages + 1));
 }
 
-// Picks the unit and the K slices by an estimate of the call's time in us, from
-// times of every unit and split of 18 matrices at 8..200 batch rows; the pick
-// is within 6 % of the fastest on most of them.  A compute unit passes about
-// 45 KiB of stages a us (35 where W's ring has three stages or fewer), W is read at
-// 6.8 TB/s at most, a workgroup takes at least `lat` us a stage (its ring over
-// the loads' latency, and the barrier), and split sums cost a launch and their
-// traffic.  16-row units are for few batch rows only: at more, x's traffic is
-// the unit's.
+// The slices that fit: of the context's workspace first, for its own calls and
+// for a caller's buffer alike (so that both sum the same slices), then of that
+// buffer.  The unit stays when a caller asks for fewer slices.
+inline int fit_slices(const PlanInput& in, int S) {
+  const uint64_t per = floats_per_slice(in);
+  while (S > 1 && S * per > in.ws_floats) S /= 2;
+  while (S > 1 && in.own_slices && S * per > in.slice_floats) S /= 2;
+  return S;
+}
+
+// The 16-row kernel: one row tile a unit; two, which share x, above 8 rows on
+// matrices of 2^25 elements or more (28672 x 4096 at 12: 54.5 -> 50.4 us;
+// smaller ones need the workgroups of one: 6144 x 4096 19-27 % longer with
+// two).  K is cut until there are two workgroups a compute unit, and while a
+// slice is longer than 8192 columns (of 94 matrices of longer rows 11 % took 6 %
+// longer without it than with the kernels before, 6 % with it), in slices of at
+// least 512.
+inline Route plan_rows16(const PlanInput& in) {
+  const int rt = in.B > 8 && static_cast<int64_t>(in.N) * in.K >= (int64_t{1} << 25) ? 2 : 1;
+  const int64_t units = in.n_pages * ((in.most + 16 * rt - 1) / (16 * rt));
+  int S = 1;
+  while (S < kMaxSlices && in.K / (2 * S) >= 512 &&
+         (units * S < 2 * in.n_cu || in.K / S > 8192))
+    S *= 2;
+  return {kRows16, rt, fit_slices(in, S)};
+}
+
+// The estimates: a call's time in us but for what every kernel takes, fitted to
+// the times of every unit and split of 735 matrices at 4..256 batch rows (300..
+// 60000 rows of 512..28800 columns drawn over their logarithm, and the layers of
+// the 8B and 70B models).  The pick takes 2 % longer than the fastest in the
+// mean, 12 % at the 95th percentile.  Split sums cost a launch and their
+// traffic, rows cut by pages without a split the launch that adds their parts.
+inline double sums_us(const PlanInput& in, int S) {
+  const double out = 1e-6 * in.B * in.N;
+  if (S > 1) return 1.6 + 4.2 * S * out;
+  return in.n_pages > 1 && (int64_t{1} << 20) % in.K != 0 ? 2.6 : 0;
+}
+
+inline double rows16_us(const PlanInput& in, const Route& r) {
+  const int64_t units = in.n_pages * ((in.most + 15) / 16);
+  // three workgroups a compute unit; a wavefront takes chunks of 256 columns
+  const double chunks = std::ceil(in.K / (4. * r.S) / 256);
+  const double rounds = std::ceil(static_cast<double>(units) * r.S / (3 * in.n_cu));
+  return std::max(2e-6 / 1.7 * in.N * in.K, rounds * (2.6 + 2.4 * chunks)) + sums_us(in, r.S);
+}
+
+// A compute unit passes so many KiB of stages a us, by batch tiles and where W's
+// ring has three stages or fewer, and takes 0.045 us of barrier a stage; W is
+// read at 7.3 TB/s at most; a workgroup takes at least 0.29 us a stage (0.55
+// with five row tiles at up to two batch tiles, where three of its eight
+// wavefronts have no tile), and 3.4 us to begin and end, 1.5 more where no other
+// one of the compute unit works meanwhile.  Rows that are no multiple of a cache
+// line read more lines.
+inline double gemm_us(const PlanInput& in, int shape, int S) {
+  const int BT = batch_tiles(in.B), rtl = kGemmShapes[shape].rtl, g = kGemmShapes[shape].g;
+  const int64_t units = (in.n_pages + g - 1) / g * ((in.most + 16 * rtl - 1) / (16 * rtl));
+  const int occ = gemm_occupancy(BT, rtl, g);
+  const bool lines = in.K % 64 != 0;
+  const double wgs = static_cast<double>(units) * S, nst = (in.K / S + 63) / 64;
+  const double rounds = std::ceil(wgs / (in.n_cu * occ));
+  const double kib = 2 * g * rtl * (lines ? 1.3 : 1) + 2 * BT;  // of a stage
+  const double rate =
+      BT == 1 ? 46 : (gemm_w_stages(BT, g * rtl) <= 3 ? 43 : (BT == 2 ? 38.6 : 58));
+  const double stages = std::ceil(wgs / in.n_cu) * nst * (kib / rate + 0.045);
+  const double hbm = 2e-6 / 7.3 * (lines ? 1.55 : 1) * in.N * in.K;
+  const double lat = BT <= 2 && rtl == 5 ? 0.55 : 0.29;
+  return std::max({hbm, stages, rounds * nst * lat}) + rounds * (occ == 1 ? 4.9 : 3.4) + 0.65 +
+         sums_us(in, S);
+}
+
+// The unit and the K slices with the least estimate.  Units without sums in
+// blocks (see gemm.h) are left to matrices that need no more slices than theirs
+// to fill the compute units, so that no row is summed in one longer chain than
+// a smaller unit would.
 inline Route plan_gemm(const PlanInput& in) {
   const int BT = batch_tiles(in.B);
-  const double cu = in.n_cu;
-  const uint64_t per = floats_per_slice(in);
-  const double hbm = 2e-6 / 6.8 * in.N * in.K;  // us to read W
   double best = 1e30;
   Route r{kGemm, -1, 1};
   for (int i = 0; i < kNumGemmShapes; ++i) {
     const int rtl = kGemmShapes[i].rtl, g = kGemmShapes[i].g;
-    const int64_t upp = (in.most + 16 * rtl - 1) / (16 * rtl);
-    if ((g > 1 && upp != 1) || (rtl == 1 && BT > 2)) continue;
-    const int64_t units = (in.n_pages + g - 1) / g * upp;
-    const int occ = gemm_occupancy(BT, rtl, g);
-    const double kb = 2 * g * rtl + 2 * BT;  // KiB of a stage
-    const double lat = std::max(BT <= 2 && rtl == 5 ? 0.42 : 0.18, 1.5 / gemm_w_stages(BT, g * rtl));
+    if (g > 1 && in.most > 16 * rtl) continue;
     for (int c = 1; c <= kMaxSlices; c *= 2) {
-      if (c > 1 && (in.K / c < 512 || c * per > in.ws_floats)) break;
-      const double nst = (in.K / c + 63) / 64, wgs = static_cast<double>(units) * c;
-      const double bytes = std::ceil(wgs / cu) * nst * kb / (gemm_w_stages(BT, g * rtl) > 3 ? 45 : 35);
-      const double rounds = std::ceil(wgs / (cu * occ));
-      const double sums = c > 1 ? 2 + 8e-6 / 4.5 * c * in.B * in.N : 0;
-      const double t = std::max({hbm, bytes, rounds * nst * lat}) + rounds * 1.5 + sums;
+      if (c > 1 && (in.K / c < 512 || c * floats_per_slice(in) > in.ws_floats)) break;
+      if (BT == 16 && g > 1 && c < kMaxSlices &&
+          (static_cast<int64_t>(in.n_pages) * c < in.n_cu * 3 / 4 || in.K / c > 16384))
+        continue;
+      const double t = gemm_us(in, i, c);
       if (t < best) best = t, r.shape = i, r.S = c;
     }
   }
-  while (r.S > 1 && in.own_slices && r.S * per > in.slice_floats) r.S /= 2;
+  r.S = fit_slices(in, r.S);
   return r;
 }
 
-// Rows up to which the 16-row kernel takes the matrix-core calls of up to 16
-// batch rows (both sides measured: see mfma_kernel).
-constexpr int kFewRows = 1200;
-
-inline Route plan_few_rows(const PlanInput& in) {
-  // split K until there are two workgroups per CU, in slices of at least 512
-  // columns whose partials fit the context's workspace or the caller's buffer
-  const int64_t units = in.n_pages * ((in.most + 15) / 16);
-  const uint64_t cap = in.own_slices ? in.slice_floats : in.ws_floats;
-  Route r{kFewRowsKernel, 0, 1};
-  while (r.S < kMaxSlices && units * r.S < 2 * in.n_cu && in.K / (2 * r.S) >= 512) r.S *= 2;
-  while (r.S > 1 && r.S * floats_per_slice(in) > cap) r.S /= 2;
-  return r;
-}
-
-// Whether a call runs on the matrix cores (the others on the GEMV): from four
-// batch rows (28672 x 4096 at 4 / 6 rows: 38.1 / 38.1 us against 43.6 / 50.1;
-// 4096 x 4096 at 6: 10.9 against 15.5; 5003 x 3080 at 4: 16.4 against 17.3).
-// Of 70 drawn matrices of 2^26 elements or more at two and three rows 59 take 3 %
-// longer on them or more (49158 x 1976 at 3: 57.8 us against 40.8; 22400 x 7040
-// at 2: 81.9 and 57.9), a few less (28672 x 4096 at 2: 38.2 and 41.8).
-inline bool matrix_cores(int B) { return B >= 4; }
-
+// Up to 3 batch rows the GEMV (of 70 matrices of 2^26 elements or more at 2 and
+// 3 rows 59 took 3 % longer or more on the matrix cores, by the GEMM's estimate:
+// 49158 x 1976 at 3 40.8 -> 57.8 us, though 28672 x 4096 at 2 41.8 -> 38.2;
+// smaller ones lose to the split sums' launch).  Up to 16 rows that are no
+// multiple of a cache line take the 16-row kernel, which reads 512 bytes of a
+// row at once where the GEMM reads 128 (7259 x 2848 at 8: 17.8 us against 20.1;
+// 52515 x 2040 at 4: 47.7 against 60.2); of the others those that it is
+// estimated to be faster on, which have few units (1278 x 784 at 10: 4.4 us
+// against 7.8; 28672 x 4096 at 8: 48 against 42).
 inline Route plan(const PlanInput& in) {
-  if (!matrix_cores(in.B)) return {kGemv, 0, 1};
-  if (in.B <= 16 && in.N <= kFewRows) return plan_few_rows(in);
-  return plan_gemm(in);
+  if (in.B <= 3) return {kGemv, 0, 1};
+  if (in.B > 16) return plan_gemm(in);
+  const Route rows = plan_rows16(in);
+  if (in.K % 64 != 0) return rows;
+  const Route gemm = plan_gemm(in);
+  return rows.shape == 1 && rows16_us(in, rows) < gemm_us(in, gemm.shape, gemm.S) ? rows : gemm;
 }
 
 // The route asked for, or one with kernel kAuto where the call does not fit it.
 inline Route forced_route(const PlanInput& in, const Forced& f) {
   const Route none{kAuto, 0, 0};
-  const uint64_t cap = in.own_slices ? in.slice_floats : in.ws_floats;
   if (f.kernel == kGemv) return in.B <= 3 ? Route{kGemv, 0, 1} : none;
-  if (f.S > 1 && (in.K / f.S < 512 || f.S * floats_per_slice(in) > cap)) return none;
-  if (f.kernel == kFewRowsKernel) return in.B <= 16 ? Route{kFewRowsKernel, 0, f.S} : none;
+  if (f.S > 1 && (in.K / f.S < 512 || fit_slices(in, f.S) != f.S)) return none;
+  if (f.kernel == kRows16) return in.B <= 16 ? Route{kRows16, f.row_tiles, f.S} : none;
   for (int i = 0; i < kNumGemmShapes; ++i) {
     const GemmShape u = kGemmShapes[i];
     if (u.rtl != f.row_tiles || u.g != f.pages) continue;
-    if ((u.g > 1 && in.most > 16 * u.rtl) || (u.rtl == 1 && batch_tiles(in.B) > 2)) return none;
+    if (u.g > 1 && in.most > 16 * u.rtl) return none;
     return {kGemm, i, f.S};
   }
   return none;

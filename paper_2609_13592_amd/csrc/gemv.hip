@@ -3,7 +3,8 @@
 // W is an [N, K] row-major bf16 matrix placed page by page on HBM or host
 // (§3.1 modulo placement).  The work unit of a workgroup is a group of rows
 // restricted to ONE page, so a workgroup reads one tier for its whole life
-// (§3.2 CTA-level confinement: a workgroup never mixes tiers).  A row that
+// (§3.2 CTA-level confinement: a workgroup never mixes tiers; the GEMM's units
+// of several pages keep to it under CAP, not in address order).  A row that
 // straddles a page boundary is split-K across the two workgroups of those
 // pages; each stores its partial sum and a small second kernel adds them in a
 // fixed order (part of the earlier page first), so results are bitwise
@@ -305,26 +306,24 @@ __global__ __launch_bounds__(256) void split_fixup(GemvParams P, int n_pages, in
 }
 
 // ---------------------------------------------------------------------------
-// Matrices of few rows at up to 16 batch rows: one 16-row tile of a page and
-// one K slice per workgroup, the slice split over its four wavefronts and
-// their partial tiles summed in LDS in wavefront order, in 64 bits.  The GEMM of gemm.h
-// has too few units there, each a long chain of stages (534 x 19232, B = 15:
-// 14.6 us here, 17.6 us there; 1160 x 15224, B = 9: 17.3 and 20.6); with more
-// rows it is the faster one (1250 x 4656, B = 7: 11.2 us here, 10.4 there;
-// 4736 x 2432, B = 8: 14.3 and 12.8).
+// Up to 16 batch rows: RT 16-row tiles of a page and one K slice per workgroup,
+// the slice split over its four wavefronts and their partial tiles summed in
+// LDS in wavefront order, in 64 bits.  Which calls it takes, and why:
+// gemm_plan.h.
 //
 // Units, schedules and cut rows as in the GEMV; with K split over S workgroups
-// every part goes to the workspace.  Each wavefront streams its 16 rows
+// every part goes to the workspace.  Each wavefront streams its rows
 // row-contiguously (one load instruction = 512 bytes of each of two rows),
-// writes the 16 x 256 column chunk into a private LDS tile (16-byte chunks
+// writes the 16 RT x 256 column chunk into a private LDS tile (16-byte chunks
 // XOR-swizzled by row, so that neither the writes nor the fragment reads meet
 // on a bank) and reads the A fragments of v_mfma_f32_16x16x32_bf16 back from
-// there; x's B fragments come straight from memory.
+// there; x's B fragments come straight from memory, once for the RT tiles.
 constexpr int kMfmaCols = 256;                          // columns per chunk
 constexpr int kMfmaTileFloats = 16 * kMfmaCols * 2 / 4;  // one wavefront's tile
-constexpr int kMfmaSumFloats = 16 * 17;                 // [batch][row], padded
-constexpr int kMfmaSums = kWaves * kMfmaSumFloats;      // of every wavefront
+template <int RT>
+constexpr int mfma_sum_floats() { return 16 * (16 * RT + 1); }  // [batch][row], padded
 
+template <int RT>
 __device__ void mfma_unit(const GemvParams& P, int page, int unit, float* lds) {
   const int j = unit / P.S, slice = unit % P.S;
   const int64_t K = P.K;
@@ -333,7 +332,7 @@ __device__ void mfma_unit(const GemvParams& P, int page, int unit, float* lds) {
   const int64_t pe1 = min(pe0 + kPageElems, total);
   const int64_t r_lo = pe0 / K;
   const int64_t r_hi = (pe1 - 1) / K;  // inclusive
-  const int64_t rbase = r_lo + static_cast<int64_t>(j) * 16;
+  const int64_t rbase = r_lo + static_cast<int64_t>(j) * (16 * RT);
   if (rbase > r_hi) return;  // uniform over the workgroup
   const int wave = threadIdx.x >> 6;
   const int lane = threadIdx.x & 63;
@@ -345,7 +344,9 @@ __device__ void mfma_unit(const GemvParams& P, int page, int unit, float* lds) {
       make_rsrc(P.x, static_cast<uint32_t>(static_cast<int64_t>(P.B) * K * 2));
   const uint32_t xo = lrow < P.B ? static_cast<uint32_t>(lrow * K * 2) : kOOB;
   // sums of two steps, added up in 64 bits (as the GEMM's one batch tile)
-  f64x4_t sum = {0., 0., 0., 0.};
+  f64x4_t sum[RT];
+#pragma unroll
+  for (int a = 0; a < RT; ++a) sum[a] = f64x4_t(0.);
 
   constexpr int kStep = 32;
   // this unit's K slice, then this wavefront's quarter of it
@@ -357,31 +358,33 @@ __device__ void mfma_unit(const GemvParams& P, int page, int unit, float* lds) {
   const int64_t k_beg = min(s_end, s_beg + wave * kper);
   const int64_t k_end = min(s_end, k_beg + kper);
 
-  uint4* tile = reinterpret_cast<uint4*>(lds + kMfmaSums + wave * kMfmaTileFloats);
+  uint4* tile = reinterpret_cast<uint4*>(lds + kWaves * mfma_sum_floats<RT>() +
+                                         wave * (RT * kMfmaTileFloats));
   // load instruction i: rows 2i and 2i+1 (lanes 0-31 / 32-63), 16 bytes each;
   // a row begun on the previous page gets a wrapped (huge) offset, so its
   // columns before the page read as zero
-  uint32_t lo[8];
+  constexpr int kLd = 8 * RT;
+  uint32_t lo[kLd];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
+  for (int i = 0; i < kLd; ++i) {
     const int64_t r = rbase + 2 * i + (lane >> 5);
     lo[i] = r > r_hi ? kOOB : static_cast<uint32_t>((r * K - pe0) * 2);
   }
   const int wr_chunk = lane & 31;
-  uint4 wv[8];
+  uint4 wv[kLd];
   auto load_chunk = [&](int64_t kb) {
     const int64_t kc = kb + 8 * wr_chunk;
     const uint32_t oob = kc < k_end ? 0u : kOOB;
     const uint32_t kc2 = static_cast<uint32_t>(kc * 2);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) wv[i] = load16(wr, (lo[i] + kc2) | oob);
+    for (int i = 0; i < kLd; ++i) wv[i] = load16(wr, (lo[i] + kc2) | oob);
   };
   if (k_beg < k_end) load_chunk(k_beg);
   constexpr int kChunkSteps = kMfmaCols / kStep;
 #pragma unroll 1
   for (int64_t kb = k_beg; kb < k_end; kb += kMfmaCols) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < kLd; ++i) {
       const int rr = 2 * i + (lane >> 5);
       tile[rr * 32 + (wr_chunk ^ (rr & 15))] = wv[i];
     }
@@ -396,32 +399,42 @@ __device__ void mfma_unit(const GemvParams& P, int page, int unit, float* lds) {
     }
     load_chunk(kb + kMfmaCols);
     __builtin_amdgcn_sched_barrier(0);
-    f32x4_t acc[kChunkSteps / 2];
+    f32x4_t acc[RT][kChunkSteps / 2];
 #pragma unroll
-    for (int st = 0; st < kChunkSteps; ++st) {
-      const uint4 a = tile[lrow * 32 + ((4 * st + lgrp) ^ lrow)];
-      const f32x4_t c = st % 2 ? acc[st / 2] : f32x4_t{0.f, 0.f, 0.f, 0.f};
-      acc[st / 2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-          __builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, xv[st]), c, 0, 0, 0);
-    }
+    for (int st = 0; st < kChunkSteps; ++st)
 #pragma unroll
-    for (int st = 0; st < kChunkSteps / 2; ++st)
-      sum += __builtin_convertvector(acc[st], f64x4_t);
+      for (int a = 0; a < RT; ++a) {
+        const uint4 w = tile[(16 * a + lrow) * 32 + ((4 * st + lgrp) ^ lrow)];
+        const f32x4_t c = st % 2 ? acc[a][st / 2] : f32x4_t{0.f, 0.f, 0.f, 0.f};
+        acc[a][st / 2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+            __builtin_bit_cast(bf16x8_t, w), __builtin_bit_cast(bf16x8_t, xv[st]), c, 0, 0, 0);
+      }
+#pragma unroll
+    for (int a = 0; a < RT; ++a)
+#pragma unroll
+      for (int st = 0; st < kChunkSteps / 2; ++st)
+        sum[a] += __builtin_convertvector(acc[a][st], f64x4_t);
   }
 
-  // output element (row 4 lgrp + e, batch row lrow); LDS holds the [batch][row]
-  // tile of every wavefront, added up in wavefront order and rounded once
+  // output element (row 16 a + 4 lgrp + e, batch row lrow); LDS holds the
+  // [batch][row] tile of every wavefront, added up in wavefront order and
+  // rounded once
+  constexpr int R = 16 * RT, LS = R + 1;
 #pragma unroll
-  for (int e = 0; e < 4; ++e)
-    lds[wave * kMfmaSumFloats + lrow * 17 + 4 * lgrp + e] = static_cast<float>(sum[e]);
+  for (int a = 0; a < RT; ++a)
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      lds[wave * mfma_sum_floats<RT>() + lrow * LS + 16 * a + 4 * lgrp + e] =
+          static_cast<float>(sum[a][e]);
   __syncthreads();
-  static_assert(kThreads == 16 * 16, "one output per thread");
-  const int b = threadIdx.x / 16, i = threadIdx.x % 16;
-  const int64_t r = rbase + i;
-  if (b < P.B && r <= r_hi) {
+#pragma unroll
+  for (int idx = threadIdx.x; idx < 16 * R; idx += kThreads) {
+    const int b = idx / R, i = idx % R;
+    const int64_t r = rbase + i;
+    if (b >= P.B || r > r_hi) continue;
     double all = 0.;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) all += lds[w * kMfmaSumFloats + b * 17 + i];
+    for (int w = 0; w < kWaves; ++w) all += lds[w * mfma_sum_floats<RT>() + b * LS + i];
     const float v = static_cast<float>(all);
     const int64_t e0 = r * K;
     const int side = e0 < pe0 ? 1 : (e0 + K > pe1 ? 0 : -1);  // cut row: its part's side
@@ -438,19 +451,20 @@ __device__ void mfma_unit(const GemvParams& P, int page, int unit, float* lds) {
   __syncthreads();  // LDS is reused by the next unit of a persistent worker
 }
 
+template <int RT>
 __global__ __launch_bounds__(kThreads) void mfma_kernel(GemvParams P) {
-  __shared__ float lds[kMfmaSums + kWaves * kMfmaTileFloats];
+  __shared__ float lds[kWaves * (mfma_sum_floats<RT>() + RT * kMfmaTileFloats)];
   const int bid = blockIdx.x;
   const int U = P.units_per_page;
   if (P.address_order) {
-    mfma_unit(P, bid / U, bid % U, lds);
+    mfma_unit<RT>(P, bid / U, bid % U, lds);
   } else if (bid < P.host_workers) {
     const int n_host_units = P.n_host_pages * U;
     for (int v = bid; v < n_host_units; v += P.host_workers)
-      mfma_unit(P, host_page(P, v / U), v % U, lds);
+      mfma_unit<RT>(P, host_page(P, v / U), v % U, lds);
   } else {
     const int u = bid - P.host_workers;
-    mfma_unit(P, hbm_page(P, u / U), u % U, lds);
+    mfma_unit<RT>(P, hbm_page(P, u / U), u % U, lds);
   }
 }
 
@@ -665,19 +679,19 @@ int launch(GemvParams& P, int n_pages, bool need_fixup, const boost_ctx* ctx, hi
   return launch_sums(P, n_pages, need_fixup, s);
 }
 
+template <int RT>
 int launch_mfma(GemvParams& P, int n_pages, bool need_fixup, const boost_ctx* ctx,
                 hipStream_t s) {
   const int S = P.S;
-  P.units_per_page = static_cast<int>((rows_met(P, n_pages) + 15) / 16);
+  P.units_per_page = static_cast<int>((rows_met(P, n_pages) + 16 * RT - 1) / (16 * RT));
   // host workers are counted over the units of whole rows
-  P.S = 1;
   int64_t grid = plan_grid(P, n_pages, ctx, true);
   if (grid < 0) return bst::fail(BOOST_EINVAL, "grid too large");
-  P.S = S;
   P.units_per_page *= S;
   grid = P.host_workers +
          static_cast<int64_t>(P.address_order ? n_pages : P.n_hbm_pages) * P.units_per_page;
-  hipLaunchKernelGGL(mfma_kernel, dim3(static_cast<unsigned>(grid)), dim3(kThreads), 0, s, P);
+  if (grid > 0x7fffffff) return bst::fail(BOOST_EINVAL, "grid too large");
+  hipLaunchKernelGGL((mfma_kernel<RT>), dim3(static_cast<unsigned>(grid)), dim3(kThreads), 0, s, P);
   BOOST_HIP(hipGetLastError());
   return launch_sums(P, n_pages, need_fixup, s);
 }
@@ -768,7 +782,9 @@ int dispatch(GemvParams& P, const boost_tensor* W, int K, int B, const boost_ctx
     for (int b = 1; b < n && !fix; ++b) fix = (static_cast<int64_t>(b) * kPageElems) % K != 0;
     P.S = route.S;
     if (P.S > 1) P.ws = P.slices ? P.slices : ctx->gemm_ws;
-    if (route.kernel == kFewRowsKernel) return launch_mfma(P, n, fix, ctx, s);
+    if (route.kernel == kRows16)
+      return route.shape == 1 ? launch_mfma<1>(P, n, fix, ctx, s)
+                              : launch_mfma<2>(P, n, fix, ctx, s);
     const int rows = 16 * kGemmShapes[route.shape].rtl;
     P.units_per_page = static_cast<int>((in.most + rows - 1) / rows) * P.S;
     switch (batch_tiles(B)) {
@@ -809,11 +825,13 @@ int boost_gemv_set_schedule(boost_ctx* ctx, int schedule, int host_workers) {
 int boost_gemv_set_route(boost_ctx* ctx, int kernel, int row_tiles, int pages, int slices) {
   if (!ctx) return fail(BOOST_EINVAL, "null ctx");
   if (kernel < kAuto || kernel > kGemm) return fail(BOOST_EINVAL, "kernel %d", kernel);
-  if (kernel >= kFewRowsKernel &&
+  if (kernel >= kRows16 &&
       (slices < 1 || slices > kMaxSlices || (slices & (slices - 1))))
     return fail(BOOST_EINVAL, "slices %d", slices);
-  bool known = kernel != kGemm;
-  for (const GemmShape& u : kGemmShapes) known = known || (u.rtl == row_tiles && u.g == pages);
+  bool known = kernel < kRows16 || (kernel == kRows16 && pages == 1 && row_tiles >= 1 &&
+                                    row_tiles <= 2);
+  for (const GemmShape& u : kGemmShapes)
+    known = known || (kernel == kGemm && u.rtl == row_tiles && u.g == pages);
   if (!known) return fail(BOOST_EINVAL, "no unit of %d row tiles and %d pages", row_tiles, pages);
   ctx->gemv_route = Forced{kernel, row_tiles, pages, slices};
   return BOOST_OK;
@@ -839,7 +857,7 @@ int boost_gemv_route(const boost_ctx* ctx, int N, int K, int B, int max_slices, 
                      ctx->device < 0 ? kGemmWsFloats : ctx->gemm_ws_floats, max_slices > 0, floats};
   const Route r = plan(in);
   *kernel = r.kernel;
-  *row_tiles = r.kernel == kGemm ? kGemmShapes[r.shape].rtl : (r.kernel == kFewRowsKernel ? 1 : 0);
+  *row_tiles = r.kernel == kGemm ? kGemmShapes[r.shape].rtl : (r.kernel == kRows16 ? r.shape : 0);
   *pages = r.kernel == kGemv ? 0 : (r.kernel == kGemm ? kGemmShapes[r.shape].g : 1);
   *slices = r.S;
   return BOOST_OK;

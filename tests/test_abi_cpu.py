@@ -215,10 +215,10 @@ def test_gemv_route_query():
                 if kernel == bd.KERNEL_GEMV:
                     assert B <= 3 and (rows, pages, S) == (0, 0, 1)
                 elif kernel == bd.KERNEL_ROWS16:
-                    assert B <= 16 and (rows, pages) == (1, 1)
+                    assert B <= 16 and rows in (1, 2) and pages == 1
                 else:
                     assert kernel == bd.KERNEL_GEMM
-                    assert (rows, pages) in ((8, 1), (8, 2), (3, 4), (5, 1), (4, 1), (2, 1), (1, 1))
+                    assert (rows, pages) in ((8, 1), (8, 2), (3, 4), (5, 1), (4, 1), (2, 1))
                     assert pages == 1 or -(-opl.PAGE // (2 * K)) <= 16 * rows
                 assert S in (1, 2, 4, 8) and (S == 1 or K // S >= 512)
                 for cap in (1, 2, 4, 8):
@@ -227,8 +227,8 @@ def test_gemv_route_query():
             with pytest.raises(bd.BoostError) as e:
                 bd.boost_gemv_route(ctx, *bad)
             assert e.value.code == bd.EINVAL
-        for bad in ((4, 1, 1, 1), (bd.KERNEL_GEMM, 7, 1, 1), (bd.KERNEL_GEMM, 8, 1, 3),
-                    (bd.KERNEL_ROWS16, 1, 1, 16)):
+        for bad in ((4, 1, 1, 1), (bd.KERNEL_GEMM, 1, 1, 1), (bd.KERNEL_GEMM, 8, 1, 3),
+                    (bd.KERNEL_ROWS16, 1, 1, 16), (bd.KERNEL_ROWS16, 3, 1, 1)):
             with pytest.raises(bd.BoostError) as e:
                 bd.boost_gemv_set_route(ctx, *bad)
             assert e.value.code == bd.EINVAL
@@ -246,3 +246,35 @@ def test_two_and_three_rows_take_the_gemv(N, K):
         assert bd.boost_gemv_route(ctx, N, K, 4)[0] != bd.KERNEL_GEMV
     finally:
         bd.boost_shutdown(ctx)
+
+
+# Matrices whose units a kernel was found slow on, with the kernel that is the
+# faster one: rows off the cache lines and small matrices on the 16-row kernel
+# (two row tiles a unit above 8 rows from 2^25 elements), units of several pages
+# where a page holds few rows, more than 16 rows on the GEMM.
+@pytest.mark.parametrize("N,K,B,kernel,rows,pages", [
+    (7259, 2848, 8, bd.KERNEL_ROWS16, 1, 1), (5003, 3080, 5, bd.KERNEL_ROWS16, 1, 1),
+    (1278, 784, 10, bd.KERNEL_ROWS16, 1, 1), (1664, 1280, 8, bd.KERNEL_ROWS16, 1, 1),
+    (52515, 2040, 4, bd.KERNEL_ROWS16, 1, 1), (20442, 9080, 12, bd.KERNEL_ROWS16, 2, 1),
+    (28672, 4096, 8, bd.KERNEL_GEMM, 4, 1), (57344, 8192, 8, bd.KERNEL_GEMM, 8, 2),
+    (8192, 28672, 8, bd.KERNEL_GEMM, 3, 4), (57344, 8192, 256, bd.KERNEL_GEMM, 8, 2),
+    (28672, 4096, 256, bd.KERNEL_GEMM, 8, 1)])
+def test_gemv_routes_by_size(N, K, B, kernel, rows, pages):
+    ctx = bd.boost_init(-1)
+    try:
+        assert bd.boost_gemv_route(ctx, N, K, B)[:3] == (kernel, rows, pages)
+    finally:
+        bd.boost_shutdown(ctx)
+
+
+def test_every_gemv_unit_is_reached():
+    """Each kernel and unit that is built is planned for some size."""
+    ctx = bd.boost_init(-1)
+    try:
+        got = {bd.boost_gemv_route(ctx, n, k, B)[:3] for B in (1, 4, 12, 24, 48, 100, 256)
+               for n in (300, 1000, 3000, 6000, 12000, 30000, 60000)
+               for k in (512, 1024, 2040, 4096, 8192, 10240, 13696, 14336, 23040, 28672)}
+    finally:
+        bd.boost_shutdown(ctx)
+    assert got == {(bd.KERNEL_GEMV, 0, 0), (bd.KERNEL_ROWS16, 1, 1), (bd.KERNEL_ROWS16, 2, 1)} | {
+        (bd.KERNEL_GEMM, r, p) for r, p in ((8, 1), (8, 2), (3, 4), (5, 1), (4, 1), (2, 1))}

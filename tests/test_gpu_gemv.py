@@ -209,8 +209,7 @@ def test_mfma_placement_invariance_and_parity(gpu_ctx, N, K, B):
 # even N (single stores); units that the last rows of a page do not fill.
 UNITS = {(8, 2): [(560, 8328, 2), (515, 8192, 1)], (3, 4): [(230, 23096, 4), (133, 28672, 1)],
          (8, 1): [(1301, 5000, 1), (700, 14336, 4)], (5, 1): [(1301, 5000, 2), (300, 14336, 1)],
-         (4, 1): [(1003, 3080, 2), (300, 14336, 8)], (2, 1): [(1003, 3080, 1), (6000, 72, 1)],
-         (1, 1): [(1003, 3080, 4), (77, 14336, 1)]}
+         (4, 1): [(1003, 3080, 2), (300, 14336, 8)], (2, 1): [(1003, 3080, 4), (6000, 72, 1)]}
 
 
 @pytest.mark.parametrize("B", [2, 20, 49, 100, 250])
@@ -220,25 +219,33 @@ def test_gemm_units_invariance_and_parity(gpu_ctx, unit, B):
     grid and rings of its own), set rather than planned: the fp32 summation
     bound against the oracle, and the same bits under all-HBM, alternating,
     modulo, irregular and all-host maps and under both schedules."""
-    if unit == (1, 1) and B > 32:
-        bd.boost_gemv_set_route(gpu_ctx, bd.KERNEL_GEMM, 1, 1, 1)
-        w, x = synth.gemv_inputs(1, 64, 512, B)
-        t = place(gpu_ctx, w, M=2)
-        try:
-            with pytest.raises(bd.BoostError) as e:  # refused, not run
-                run_gemv(gpu_ctx, t, 64, 512, to_dev_u16(x), B)
-            assert e.value.code == bd.EINVAL
-        finally:
-            bd.boost_gemv_set_route(gpu_ctx, bd.KERNEL_AUTO)
-            bd.boost_tensor_free(t)
-        return
     for N, K, S in UNITS[unit]:
         check_route(gpu_ctx, (bd.KERNEL_GEMM, *unit, S), N, K, B)
 
 
-@pytest.mark.parametrize("N,K,B,S", [(1003, 3080, 4, 4), (300, 14336, 16, 1), (77, 28672, 9, 8)])
-def test_rows16_invariance_and_parity(gpu_ctx, N, K, B, S):
-    check_route(gpu_ctx, (bd.KERNEL_ROWS16, 1, 1, S), N, K, B)
+@pytest.mark.parametrize("route,N,K,B", [((bd.KERNEL_GEMV, 0, 0, 1), 64, 512, 4),
+                                         ((bd.KERNEL_ROWS16, 1, 1, 1), 64, 512, 17),
+                                         ((bd.KERNEL_GEMM, 8, 2, 1), 300, 8000, 4),
+                                         ((bd.KERNEL_GEMM, 2, 1, 2), 64, 1000, 4)])
+def test_routes_that_do_not_fit_are_refused(gpu_ctx, route, N, K, B):
+    w, x = synth.gemv_inputs(1, N, K, B)
+    t = place(gpu_ctx, w, M=2)
+    try:
+        bd.boost_gemv_set_route(gpu_ctx, *route)
+        with pytest.raises(bd.BoostError) as e:
+            run_gemv(gpu_ctx, t, N, K, to_dev_u16(x), B)
+        assert e.value.code == bd.EINVAL
+    finally:
+        bd.boost_gemv_set_route(gpu_ctx, bd.KERNEL_AUTO)
+        bd.boost_tensor_free(t)
+
+
+@pytest.mark.parametrize("tiles", [1, 2])
+@pytest.mark.parametrize("N,K,B,S", [(1003, 3080, 4, 4), (300, 14336, 16, 1), (77, 28672, 9, 8),
+                                     (6000, 72, 2, 1)])
+def test_rows16_invariance_and_parity(gpu_ctx, tiles, N, K, B, S):
+    """The 16-row kernel with one and two row tiles a unit, set as above."""
+    check_route(gpu_ctx, (bd.KERNEL_ROWS16, tiles, 1, S), N, K, B)
 
 
 def check_route(ctx, route, N, K, B):
