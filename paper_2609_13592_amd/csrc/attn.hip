@@ -60,7 +60,9 @@ constexpr int kPartMin = BOOST_ATTN_PART_MIN, kPartMax = BOOST_ATTN_PART_MAX;
 // down to four blocks: a longer chain of loads on some units is then worse
 // than the starts and ends of more items (32 / 8 heads, one request of 500 /
 // 2048 tokens: 16.6 / 17.1 -> 10.0 / 11.6 us, four of 200..1000: 16.8 -> 11.4;
-// with enough items it loses, one of 8192: 19.2 -> 20.7).
+// with enough items it loses, one of 8192: 19.2 -> 20.7).  The items are
+// counted from the width of the block table, since the host does not know the
+// context lengths: short contexts in a wide table keep kPartMin.
 constexpr int kPartFew = 4;
 
 struct AttnParams {
@@ -241,7 +243,7 @@ __device__ __forceinline__ void consume(const uint32_t (*qp)[4], const uint4* kb
 // query head) are reduced over the token's 16 lanes by a transposing
 // butterfly: exchange with the lane xor 1 (and xor 2 for groups of four)
 // keeping half the heads each time, then add the lanes 4 and 8 apart, so each
-// lane ends with the full score of ONE head of a group (head_of_lane) instead
+// lane ends with the full score of ONE head of a group (lane_of_head) instead
 // of every lane holding all of them.  The running maximum, the exponentials
 // and the running sum are then computed once per head and token instead of 16
 // times; the probabilities and rescale factors reach the other lanes'
@@ -249,11 +251,6 @@ __device__ __forceinline__ void consume(const uint32_t (*qp)[4], const uint4* kb
 // vector instructions per block (at G = 8, 190 -> 140).
 template <int G>
 constexpr int hd_group() { return G == 8 ? 4 : G; }
-template <int G>
-__device__ __forceinline__ int head_of_lane(int lane) {
-  const int i = lane & 3;
-  return G == 4 ? 2 * (i & 1) + (i >> 1) : (i & 1);
-}
 // the lane of a quad that holds head j (the map is its own inverse)
 template <int G>
 constexpr int lane_of_head(int j) { return G == 4 ? 2 * (j & 1) + (j >> 1) : j; }
@@ -634,7 +631,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
   const uint64_t head_off = static_cast<uint64_t>(g) * P.nb * (kT * kD * 2);
   // q stays in bf16 pairs for the dot2 instruction
   // (G = 8: in LDS, since the accumulators and a group's K and V leave no
-  // registers for them at three waves per SIMD)
+  // registers for them at two waves per SIMD)
   constexpr bool kQLds = G == 8;
   __shared__ uint4 s_q[kQLds ? G * kLanesTok : 1];
   uint32_t qp[kQLds ? 1 : G][4];
@@ -677,7 +674,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[j][e] = 0.f;
   }
-  // head-distributed state (G = 2, 4): this lane's head's maximum and sum
+  // head-distributed state (G = 2, 4, 8): the maximum and sum of this lane's
+  // head of each group
   constexpr bool kHD = G >= 2;
   constexpr int kHG = kHD ? G / hd_group<G>() : 1;
   const bool b0 = tid & 1, b1 = tid & 2;

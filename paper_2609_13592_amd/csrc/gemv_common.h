@@ -125,7 +125,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc_uniform(const void* 
 }
 
 // Offsets at or above this are outside every resource used here (a page is
-// 2 MiB, x is at most 8 * 512 K elements), so the load returns zero.
+// 2 MiB, x at most 256 rows of 2^20 elements, 2^29 bytes), so the load returns
+// zero.
 constexpr uint32_t kOOB = 0x80000000u;
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
