@@ -328,16 +328,16 @@ __device__ __forceinline__ void gemm_dma_unit(const GemvParams& P, int page_in, 
       for (int a = 0; a < RW; ++a)
         acc[a][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.w[a], f.x[t], acc[a][t], 0, 0, 0);
   };
-  // Sums in blocks of `block` stages (a power of two): the running sums of a
+  // Sums in blocks of `block` stages: the running sums of a
   // block are added to `sum` and begun anew, since one chain over a long slice
   // rounds at the size of the whole sum at every step (8192 x 28672 at 8 rows:
-  // relative error 7.5e-7 as one chain).  Eight blocks a slice, of 512 columns
-  // at least: with sqrt(n) blocks of the n steps, sums of 64 columns err half
-  // as much and cost 4-6 % of the time at 17 rows and more, these 1 %.  One
-  // batch tile (two or three tiles a wavefront) adds every stage to sums of 64
-  // bits, so that the error does not grow with K at all: the GEMV, which takes
-  // the smaller batches, sums over 64 lanes and errs no more (4096 columns:
-  // 9e-8; 6.5e-8 here).  That costs 1 %.
+  // relative error 7.5e-7 as one chain).  P.parts blocks and slices a row in
+  // all, of 512 columns at least: with sqrt(n) blocks of the n steps, sums of 64
+  // columns err half as much and cost 4-6 % of the time at 17 rows and more,
+  // these 1 %.  One batch tile (two or three tiles a wavefront) adds every stage
+  // to sums of 64 bits, so that the error does not grow with K at all: the GEMV,
+  // which takes the smaller batches, sums over 64 lanes and errs no more (4096
+  // columns: 9e-8; 6.5e-8 here).  That costs 1 %.
   constexpr bool kBlocks = C::kBlocks, kWide = BT == 1;
   using sum_t = typename std::conditional<kWide, f64x4_t, f32x4_t>::type;
   sum_t sum[kBlocks ? RW : 1][kBlocks ? BW : 1];
@@ -358,9 +358,7 @@ __device__ __forceinline__ void gemm_dma_unit(const GemvParams& P, int page_in, 
         }
     }
   };
-  int block = 8;
-  while (8 * block < nst) block *= 2;
-  if (!kBlocks || kWide) block = nst;
+  const int block = kBlocks && !kWide ? max(8, (nst * P.S + P.parts - 1) / P.parts) : nst;
 
   // A stage is two 32-column steps; the fragments of a step are read while
   // the matrix cores work on the step before it (two register sets), and the
@@ -490,6 +488,10 @@ int launch_gemm_shape(GemvParams& P, int n_pages, bool need_fixup, const boost_c
   const int64_t groups = (n_pages + G - 1) / G;
   P.vec_out = P.N % 4 == 0 && (reinterpret_cast<uintptr_t>(P.S > 1 ? P.ws : P.y) & 15) == 0;
   P.w_once = P.K % 64 == 0;
+  // sums a row: the kernels before cut K, into up to eight slices, where it was
+  // longer than 16 K or where 64-row units were fewer than three quarters of the
+  // compute units; twice as many here
+  P.parts = n_pages < ctx->n_cu * 3 / 8 || P.K > 65536 ? 16 : 4;
   int64_t grid;
   if (P.address_order || P.n_host_pages == 0) {
     P.address_order = 1;

@@ -16,8 +16,10 @@ constexpr int kMaxSlices = 8;
 // 10240 x 8192 at 8 rows 29.4 us with four, 31.6 with eight; 28672 x 4096 at
 // 256 rows 74 us with eight, 82 with four), and the stages of x and of W in
 // its rings: 8..16 of both while two workgroups fit a compute unit (small
-// units live off their depth), else four of x and up to seven of W, three and
-// two of x where it takes 32 KiB a stage.
+// units live off their depth), else four of x and up to seven of W, six where
+// two workgroups fit then (64-row units at 64 rows: 2048 x 24064 at 42 44.1 us
+// with seven and one workgroup), three and two of x where it takes 32 KiB a
+// stage.
 constexpr int gemm_waves(int bt, int rtl, int g) {
   if (g > 1) return 8;
   if (rtl == 5) return bt == 4 ? 4 : 8;
@@ -31,7 +33,8 @@ constexpr int gemm_x_stages(int bt, int rows) {
 constexpr int gemm_w_stages(int bt, int rows) {
   const int xs = gemm_x_stages(bt, rows);
   if (xs >= 8) return xs;
-  const int fit = (kDmaLds / kDmaBlk - xs * 2 * bt) / (2 * rows);
+  const int two = (kDmaLds / kDmaBlk / 2 - xs * 2 * bt) / (2 * rows);
+  const int fit = two >= 6 ? two : (kDmaLds / kDmaBlk - xs * 2 * bt) / (2 * rows);
   return fit < 7 ? fit : 7;
 }
 // A host sub-unit (one row tile) loads W in spans of kSpan stages, 512 bytes of
@@ -116,15 +119,28 @@ inline Route plan_rows16(const PlanInput& in) {
 }
 
 // The estimates: a call's time in us but for what every kernel takes, fitted to
-// the times of every unit and split of 735 matrices at 4..256 batch rows (300..
+// the times of every unit and split of 1540 matrices at 4..256 batch rows (300..
 // 60000 rows of 512..28800 columns drawn over their logarithm, and the layers of
-// the 8B and 70B models).  The pick takes 2 % longer than the fastest in the
-// mean, 12 % at the 95th percentile.  Split sums cost a launch and their
-// traffic, rows cut by pages without a split the launch that adds their parts.
-inline double sums_us(const PlanInput& in, int S) {
-  const double out = 1e-6 * in.B * in.N;
-  if (S > 1) return 1.6 + 4.2 * S * out;
-  return in.n_pages > 1 && (int64_t{1} << 20) % in.K != 0 ? 2.6 : 0;
+// the 8B and 70B models).  The pick takes 1-3 % longer than the fastest in the
+// mean, 8-13 % at the 95th percentile.
+//
+// What a workgroup of the GEMM takes, with one batch tile and with more (W is
+// the stream then, or W and x are): W's rate (TB/s) and the lines that ragged
+// rows read more; the stages' rate (KiB a us and compute unit) and barrier; the
+// least time of a stage, and the time that W's and x's ring cover; the least with
+// five row tiles at up to two batch tiles, where three of eight wavefronts have
+// none; beginning and end, and more where no other workgroup of the compute unit
+// works meanwhile; the sums' launch (us) and traffic (us a MiB of slices), and
+// the launch that joins cut rows.
+struct GemmCost {
+  double hbm, ragged, barrier, stage, w_ring, x_ring, stage5, begin, alone, split, slices, cut;
+};
+constexpr GemmCost kOneTile{7.3, 1.55, 0.045, 0.29, 0, 0, 0.55, 3.4, 1.5, 1.6, 4.2, 2.6};
+constexpr GemmCost kMoreTiles{7.26, 1.18, 0.027, 0.27, 2.44, 1.37, 0.4, 2.43, 2.27, 2.1, 4.5, 1.9};
+
+inline double sums_us(const PlanInput& in, int S, const GemmCost& c) {
+  if (S > 1) return c.split + c.slices * S * 1e-6 * in.B * in.N;
+  return in.n_pages > 1 && (int64_t{1} << 20) % in.K != 0 ? c.cut : 0;
 }
 
 inline double rows16_us(const PlanInput& in, const Route& r) {
@@ -132,31 +148,26 @@ inline double rows16_us(const PlanInput& in, const Route& r) {
   // three workgroups a compute unit; a wavefront takes chunks of 256 columns
   const double chunks = std::ceil(in.K / (4. * r.S) / 256);
   const double rounds = std::ceil(static_cast<double>(units) * r.S / (3 * in.n_cu));
-  return std::max(2e-6 / 1.7 * in.N * in.K, rounds * (2.6 + 2.4 * chunks)) + sums_us(in, r.S);
+  return std::max(2e-6 / 2.6 * in.N * in.K, rounds * (2.6 + 2.4 * chunks)) +
+         sums_us(in, r.S, kOneTile);
 }
 
-// A compute unit passes so many KiB of stages a us, by batch tiles and where W's
-// ring has three stages or fewer, and takes 0.045 us of barrier a stage; W is
-// read at 7.3 TB/s at most; a workgroup takes at least 0.29 us a stage (0.55
-// with five row tiles at up to two batch tiles, where three of its eight
-// wavefronts have no tile), and 3.4 us to begin and end, 1.5 more where no other
-// one of the compute unit works meanwhile.  Rows that are no multiple of a cache
-// line read more lines.
 inline double gemm_us(const PlanInput& in, int shape, int S) {
   const int BT = batch_tiles(in.B), rtl = kGemmShapes[shape].rtl, g = kGemmShapes[shape].g;
+  const GemmCost& c = BT == 1 ? kOneTile : kMoreTiles;
   const int64_t units = (in.n_pages + g - 1) / g * ((in.most + 16 * rtl - 1) / (16 * rtl));
-  const int occ = gemm_occupancy(BT, rtl, g);
-  const bool lines = in.K % 64 != 0;
+  const int occ = gemm_occupancy(BT, rtl, g), ring = gemm_w_stages(BT, g * rtl);
+  const bool ragged = in.K % 64 != 0;
   const double wgs = static_cast<double>(units) * S, nst = (in.K / S + 63) / 64;
   const double rounds = std::ceil(wgs / (in.n_cu * occ));
-  const double kib = 2 * g * rtl * (lines ? 1.3 : 1) + 2 * BT;  // of a stage
-  const double rate =
-      BT == 1 ? 46 : (gemm_w_stages(BT, g * rtl) <= 3 ? 43 : (BT == 2 ? 38.6 : 58));
-  const double stages = std::ceil(wgs / in.n_cu) * nst * (kib / rate + 0.045);
-  const double hbm = 2e-6 / 7.3 * (lines ? 1.55 : 1) * in.N * in.K;
-  const double lat = BT <= 2 && rtl == 5 ? 0.55 : 0.29;
-  return std::max({hbm, stages, rounds * nst * lat}) + rounds * (occ == 1 ? 4.9 : 3.4) + 0.65 +
-         sums_us(in, S);
+  const double kib = 2 * g * rtl * (ragged ? 1.3 : 1) + 2 * BT;  // of a stage
+  const double rate = BT == 1 ? 46 : (ring <= 3 ? 39 : (BT == 2 ? 47 : 51));
+  const double stages = std::ceil(wgs / in.n_cu) * nst * (kib / rate + c.barrier);
+  double stage = std::max({c.stage, c.w_ring / ring, c.x_ring / gemm_x_stages(BT, g * rtl)});
+  if (BT <= 2 && rtl == 5) stage = std::max(stage, c.stage5);
+  const double hbm = 2e-6 / c.hbm * (ragged ? c.ragged : 1) * in.N * in.K;
+  return std::max({hbm, stages, rounds * nst * stage}) +
+         rounds * (c.begin + (occ == 1 ? c.alone : 0)) + 0.65 + sums_us(in, S, c);
 }
 
 // The unit and the K slices with the least estimate.  Units without sums in

@@ -38,6 +38,7 @@ struct GemvParams {
   int join;  // 1: a cut row between two pages of one tier is summed by one unit
   int tail_first;  // 1: the last unit of every page is dispatched before the others
   int S;     // K slices per row group (matrix-core path; 1 = no split)
+  int parts;    // partial sums of a row (blocks of all slices; matrix-core GEMM)
   int w_once;   // 1: no two column stages of W share a 128-byte line (streaming loads)
   int vec_out;  // 1: four consecutive outputs of a batch row may go out in one store
   float* ws;  // S > 1 (16-byte aligned): [S][B][N] partials, then [(n_pages + 1) * 2][S][B] of cut rows
