@@ -26,15 +26,15 @@
 // cross-wavefront reduction.  Rows cut by a page boundary and split-K slices
 // go through partial buffers that launch_sums (or the consumer) adds in order.
 //
-// What bounds it: W's stream up to about 32 batch rows (28672 x 4096: 37-38
-// us, 6.3 TB/s at 8..32 rows, against 43.9 at 8 and 48.3 at 16 for 16-row
-// units that staged W through registers), then the requests that a compute
-// unit's L1 keeps in flight, of which x takes 2 BT and W 2 G RTL KiB a stage
-// (the same matrix at 64 / 128 / 256 rows: 40 / 51 / 74 us; 56 / 63 / 88
+// What bounds it: W's stream up to about 32 batch rows (28672 x 4096: 41-42
+// us, 5.7 TB/s at 4..32 rows in cold weights, against 46 at 8 and 50 at 16 for
+// 16-row units that staged W through registers), then the requests that a
+// compute unit's L1 keeps in flight, of which x takes 2 BT and W 2 G RTL KiB a
+// stage (the same matrix at 64 / 128 / 256 rows: 44 / 55 / 77 us; 59 / 69 / 90
 // before the two roles, the start columns, the step-ahead fragment reads and
 // the conflict-free layout).  So a unit holds as many rows as the grid allows:
 // two pages of 8192 columns (57344 x 8192, 256 rows: 257 us, 287 with one
-// page), four of 28672 (8192 x 28672, 64 rows: 85 us; 131 with 64-row units).
+// page), four of 28672 (8192 x 28672, 64 rows: 94-100 us; 145 with 64-row units).
 #include <algorithm>
 #include <type_traits>
 
