@@ -119,10 +119,10 @@ inline Route plan_rows16(const PlanInput& in) {
 }
 
 // The estimates: a call's time in us but for what every kernel takes, fitted to
-// the times of every unit and split of 1540 matrices at 4..256 batch rows (300..
+// the times of every unit and split of 2600 matrices at 4..256 batch rows (300..
 // 60000 rows of 512..28800 columns drawn over their logarithm, and the layers of
-// the 8B and 70B models).  The pick takes 1-3 % longer than the fastest in the
-// mean, 8-13 % at the 95th percentile.
+// the 8B and 70B models).  The pick takes 0.6 % longer than the fastest in the
+// mean (3 % up to 16 rows), 5 % at the 95th percentile (13 %).
 //
 // What a workgroup of the GEMM takes, with one batch tile and with more (W is
 // the stream then, or W and x are): W's rate (TB/s) and the lines that ragged
@@ -143,8 +143,19 @@ inline double sums_us(const PlanInput& in, int S, const GemmCost& c) {
   return in.n_pages > 1 && (int64_t{1} << 20) % in.K != 0 ? c.cut : 0;
 }
 
+// Units of `rows` rows of each of g pages that hold rows: one more than the
+// compute units is a round more, so those of the last page are counted (28187 x
+// 1584 at 144 rows, 128-row units: 256 of 258 places, 51.7 us; 66 with the
+// 64-row units that seemed faster).
+inline int64_t units_of(const PlanInput& in, int rows, int g) {
+  if (g > 1) return (in.n_pages + g - 1) / g;
+  const int64_t page = int64_t{1} << 20, total = static_cast<int64_t>(in.N) * in.K;
+  const int64_t last = (total - 1) / in.K - (in.n_pages - 1) * page / in.K + 1;
+  return (in.n_pages - 1) * ((in.most + rows - 1) / rows) + (last + rows - 1) / rows;
+}
+
 inline double rows16_us(const PlanInput& in, const Route& r) {
-  const int64_t units = in.n_pages * ((in.most + 15) / 16);
+  const int64_t units = units_of(in, 16, 1);
   // three workgroups a compute unit; a wavefront takes chunks of 256 columns
   const double chunks = std::ceil(in.K / (4. * r.S) / 256);
   const double rounds = std::ceil(static_cast<double>(units) * r.S / (3 * in.n_cu));
@@ -155,7 +166,7 @@ inline double rows16_us(const PlanInput& in, const Route& r) {
 inline double gemm_us(const PlanInput& in, int shape, int S) {
   const int BT = batch_tiles(in.B), rtl = kGemmShapes[shape].rtl, g = kGemmShapes[shape].g;
   const GemmCost& c = BT == 1 ? kOneTile : kMoreTiles;
-  const int64_t units = (in.n_pages + g - 1) / g * ((in.most + 16 * rtl - 1) / (16 * rtl));
+  const int64_t units = units_of(in, 16 * rtl, g);
   const int occ = gemm_occupancy(BT, rtl, g), ring = gemm_w_stages(BT, g * rtl);
   const bool ragged = in.K % 64 != 0;
   const double wgs = static_cast<double>(units) * S, nst = (in.K / S + 63) / 64;

@@ -258,7 +258,9 @@ def test_two_and_three_rows_take_the_gemv(N, K):
     (52515, 2040, 4, bd.KERNEL_ROWS16, 1, 1), (20442, 9080, 12, bd.KERNEL_ROWS16, 2, 1),
     (28672, 4096, 8, bd.KERNEL_GEMM, 4, 1), (57344, 8192, 8, bd.KERNEL_GEMM, 8, 2),
     (8192, 28672, 8, bd.KERNEL_GEMM, 3, 4), (57344, 8192, 256, bd.KERNEL_GEMM, 8, 2),
-    (28672, 4096, 256, bd.KERNEL_GEMM, 8, 1)])
+    (28672, 4096, 256, bd.KERNEL_GEMM, 8, 1),
+    # 256 units that hold rows in 258 places: one round
+    (28187, 1584, 144, bd.KERNEL_GEMM, 8, 1)])
 def test_gemv_routes_by_size(N, K, B, kernel, rows, pages):
     ctx = bd.boost_init(-1)
     try:
